@@ -6,6 +6,7 @@
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -505,7 +506,15 @@ static void launch_skinny_ln(const LinArgs& a, hipStream_t s) {
 // c ^ swz(r), so the 16 rows one MFMA operand read touches cover every bank
 // once.  Tiles are visited in groups of 8 row tiles, and consecutive groups
 // of the launch order land on one XCD, so the A and W tiles a group shares
-// stay in that XCD's L2.
+// stay in that XCD's L2.  Two operand register sets: the fragments of the
+// next 32-wide step are read from LDS under the current step's MFMAs, and the
+// stage's one barrier sits between its two steps, with a step's products
+// ready to run behind it.  A chunk's first products start from a zero operand
+// and its sums join the totals under the last step's MFMAs.  Measured, us
+// (before: 128 x 128 tiles of 4 waves, one operand set): 8192 x 2048 x 8192
+// with the residual 285 -> 249 (1100 TFLOP/s; MFMA busy 56% of the cycles,
+// at the 1.92 GHz that this load leaves), 8192 x 8192 x 2048 with GELU 323 ->
+// 306, 8192 x 3072 x 1024 61 -> 57.
 template <int BM_, int BN_, int BK_, int NS_, int WAVES_M, int WAVES_N>
 struct GemmCfg {
   static constexpr int BM = BM_, BN = BN_, BK = BK_, NS = NS_;
@@ -530,9 +539,10 @@ __device__ __forceinline__ void wait_stages(int ahead) {
 }
 
 template <int EPI, class C>
-__global__ void __launch_bounds__(C::NT, 2 * 4 / C::NW) k_gemm(LinArgs a, int tiles_m, int tiles_n) {
+__global__ void __launch_bounds__(C::NT, 2) k_gemm(LinArgs a, int tiles_m, int tiles_n) {
   constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NS = C::NS, WM = C::WM, WN = C::WN;
-  constexpr int TM = C::TM, TN = C::TN, IA = C::IA, IB = C::IB, STAGE = C::STAGE;
+  constexpr int TM = C::TM, TN = C::TN, IA = C::IA, IB = C::IB, STAGE = C::STAGE, KSS = BK / 32;
+  static_assert(KSS % 2 == 0, "the next stage's first step goes to operand set 0");
   __shared__ __attribute__((aligned(1024))) uint16_t lds[NS * STAGE];
   // launch order -> tile: consecutive pids of one XCD, then groups of 8 row tiles
   const int pid = xcd_order(blockIdx.x, tiles_m * tiles_n);
@@ -556,53 +566,97 @@ __global__ void __launch_bounds__(C::NT, 2 * 4 / C::NW) k_gemm(LinArgs a, int ti
     gb[i] = lin_wrow(a, min(n0 + r, a.N - 1)) + c * 8;
   }
   const uint32_t lbase = (uint32_t)(uintptr_t)lds;
-  auto issue = [&](int kt) {
-    const uint32_t sb = lbase + (uint32_t)((kt % NS) * STAGE * 2);
+  // the ring's stages in LDS bytes: the one read next, the one filled next
+  uint32_t rd = 0, wr = 0;
+  auto turn = [](uint32_t x) { return x + STAGE * 2 == NS * STAGE * 2 ? 0u : x + STAGE * 2; };
+  auto issue = [&]() {                   // the next stage of K
+    const uint32_t sb = lbase + wr;
 #pragma unroll
-    for (int i = 0; i < IA; ++i)
-      dma16(ga[i] + kt * BK, __builtin_amdgcn_readfirstlane(sb + (wave * IA + i) * 1024));
+    for (int i = 0; i < IA; ++i) {
+      dma16(ga[i], __builtin_amdgcn_readfirstlane(sb + (wave * IA + i) * 1024));
+      ga[i] += BK;
+    }
 #pragma unroll
-    for (int i = 0; i < IB; ++i)
-      dma16(gb[i] + kt * BK, __builtin_amdgcn_readfirstlane(sb + BM * BK * 2 + (wave * IB + i) * 1024));
+    for (int i = 0; i < IB; ++i) {
+      dma16(gb[i], __builtin_amdgcn_readfirstlane(sb + BM * BK * 2 + (wave * IB + i) * 1024));
+      gb[i] += BK;
+    }
+    wr = turn(wr);
   };
   f32x4 acc[TM][TN], tot[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int p = 0; p < NS - 1 && p < KT; ++p) issue(p);
-  for (int kt = 0; kt < KT; ++kt) {
-    wait_stages<IA + IB>(min(NS - 2, KT - 1 - kt));
-    lds_barrier();                       // stage kt is in LDS; every wave is done with stage kt - 1
-    if (kt + NS - 1 < KT) issue(kt + NS - 1);
-    const uint16_t* sa = lds + (kt % NS) * STAGE;
-    const uint16_t* sb = sa + BM * BK;
+    for (int j = 0; j < TN; ++j) tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // operand registers, two sets: one 32-wide step's fragments are read from
+  // LDS while the other's MFMAs run
+  u32x4 A[2][TM], B[2][TN];
+  // A tile's operand rows are 16 apart, which leaves their swizzle alone (swz
+  // has period 16), and the second step's slots are the first's with bit 2
+  // flipped: one LDS address per operand and step, the tiles at fixed offsets.
+  static_assert(C::swz(16) == 0 && C::CPR == 8, "operand addresses");
+  const int la = (wm * WM + (lane & 15)) * BK, lb = BM * BK + (wn * WN + (lane & 15)) * BK;
+  const int sl = ((lane >> 4) ^ C::swz(lane & 15)) << 3;
+  auto read = [&](int set, int ks) {
+    const uint16_t* st = lds + rd / 2 + (sl ^ (ks << 5));
 #pragma unroll
-    for (int ks = 0; ks < BK / 32; ++ks) {
-      const int c = ks * 4 + (lane >> 4);
-      u32x4 B[TN];
+    for (int j = 0; j < TN; ++j) B[set][j] = *(const u32x4*)(st + lb + j * 16 * BK);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int r = wn * WN + j * 16 + (lane & 15);
-        B[j] = *(const u32x4*)(sb + r * BK + ((c ^ C::swz(r)) << 3));
+    for (int i = 0; i < TM; ++i) A[set][i] = *(const u32x4*)(st + la + i * 16 * BK);
+  };
+  // One stage of a chunk.  FIRST: its first step starts the chunk's sums from
+  // zero; LAST: its last step adds them to the totals, each row of tiles
+  // behind the next row's MFMAs.
+  auto stage = [&](auto first, auto last, int kt) {
+    constexpr bool FIRST = decltype(first)::value, LAST = decltype(last)::value;
+    if (kt + NS - 1 < KT) issue();
+#pragma unroll
+    for (int ks = 0; ks < KSS; ++ks) {
+      if (ks + 1 < KSS) {
+        read((ks + 1) & 1, ks + 1);
+      } else {
+        // stage kt + 1 has landed for every wave, and every wave has read
+        // stage kt (behind the last stage this reads a stale one, unused)
+        wait_stages<IA + IB>(min(NS - 2, KT - 2 - kt));
+        lds_barrier();
+        rd = turn(rd);
+        read((ks + 1) & 1, 0);
       }
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const int r = wm * WM + i * 16 + (lane & 15);
-        const u32x4 A = *(const u32x4*)(sa + r * BK + ((c ^ C::swz(r)) << 3));
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma16(B[j], A, acc[i][j]);
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = mfma16(B[ks & 1][j], A[ks & 1][i], FIRST && ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][j]);
+        if (LAST && ks + 1 == KSS && i > 0) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j) tot[i - 1][j] += acc[i - 1][j];
+        }
+      }
+      if (LAST && ks + 1 == KSS) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) tot[TM - 1][j] += acc[TM - 1][j];
       }
     }
-    if ((kt + 1) % CT == 0 || kt + 1 == KT) {
+  };
+  for (int p = 0; p < NS - 1 && p < KT; ++p) issue();
+  wait_stages<IA + IB>(min(NS - 2, KT - 1));
+  lds_barrier();
+  read(0, 0);
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  int kt = 0;
+  for (const int full = KT - KT % CT; kt < full;) {
+    stage(yes, no, kt);
+    for (int e = kt + CT - 1; ++kt < e;) stage(no, no, kt);
+    stage(no, yes, kt++);
+  }
+  if (kt < KT) {                         // a last, shorter chunk
+    stage(yes, no, kt);
+    while (++kt < KT) stage(no, no, kt);
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          tot[i][j] += acc[i][j];
-          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-    }
+      for (int j = 0; j < TN; ++j) tot[i][j] += acc[i][j];
   }
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
@@ -743,22 +797,34 @@ static void launch_gemm(const LinArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((k_gemm<EPI, C>), dim3(xcd_grid(tm * tn)), dim3(C::NT), 0, s, a, tm, tn);
 }
 
-#ifndef GEMM_BIG
-#define GEMM_BIG GemmCfg<128, 128, 64, 2, 2, 2>
-#endif
-#ifndef GEMM_MID
-#define GEMM_MID GemmCfg<64, 64, 64, 2, 2, 2>
-#endif
-// Mid tiles over a long reduction (K >= 3072): with one or two workgroups per
-// CU the stage wait is the critical path, so four stages are kept in flight
-// (measured 24.8 against 31.8 us for 1024 x 1024 x 4096; for K <= 2048 the
-// deeper ring's prologue and LDS cost more than it saves).
-#ifndef GEMM_MID_DEEP
-#define GEMM_MID_DEEP GemmCfg<64, 64, 64, 4, 2, 2>
-#endif
-using GemmBig = GEMM_BIG;
-using GemmMid = GEMM_MID;
-using GemmMidDeep = GEMM_MID_DEEP;
+// The tiles of a many-row map.  A wide tile moves fewer bytes from L2 into
+// LDS per product (the DMA, not the LDS reads, is what the main loop waits
+// for: with it taken out the 128 x 256 loop runs at 1420 instead of 1080
+// TFLOP/s), a small one fills the 256 CUs on small outputs.
+using GemmWide = GemmCfg<128, 256, 64, 3, 2, 4>;   // one workgroup of 8 waves per CU (144 KB of LDS)
+using GemmTall = GemmCfg<128, 128, 64, 4, 2, 4>;   // one of 8 waves per CU (128 KB)
+using GemmPair = GemmCfg<128, 128, 64, 2, 2, 2>;   // two of 4 waves per CU (64 KB each)
+using GemmSmall = GemmCfg<64, 64, 64, 4, 2, 2>;    // two of 4 waves per CU (64 KB each)
+enum GemmTile { kGemmWide, kGemmTall, kGemmPair, kGemmSmall };
+
+// The tile of an M x N map: the cheapest by rounds over the 256 CUs, a round
+// priced in rounds of the wide tile as measured (K 1024 .. 8192: 128 x 128
+// with 8 waves 0.56; 64 x 64 0.37 with one workgroup per CU and 0.45 with
+// two).  128 x 128 tiles that spill a little over one round go two to a CU
+// instead (0.85 up to 384 tiles: 520 x 8192 x 2048 33.9 us against 41.8 on
+// the wide tile).  us on wide / tall / pair / small tiles: 8192 x 1024 x 4096
+// 70.6 / - / 80.1 / -, 4096 x 3072 x 1024 36.4 / 33.6 / 35.5 / 44.2, 2048 x
+// 2048 x 2048 31.4 / 22.6 / 32.0 / 29.0, 1024 x 4096 x 1024 20.3 / 14.1 /
+// 19.1 / 17.0, 1024 x 1024 x 4096 50.3 / 33.4 / 52.7 / 19.5.
+inline GemmTile gemm_tile(int M, int N) {
+  auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const long wide = tiles(128, 256), tall = tiles(128, 128), small = tiles(64, 64);
+  const long c_wide = (wide + 255) / 256 * 100, c_tall = (tall + 255) / 256 * 56;
+  const long c_pair = tall > 256 && tall <= 384 ? 85 : c_tall + 1;
+  const long c_small = small <= 256 ? 37 : (small + 511) / 512 * 45;
+  const long best = std::min(std::min(c_wide, c_tall), std::min(c_pair, c_small));
+  return best == c_small ? kGemmSmall : best == c_tall ? kGemmTall : best == c_pair ? kGemmPair : kGemmWide;
+}
 
 template <int EPI>
 static hipError_t linear(const LinArgs& a, hipStream_t s) {
@@ -785,12 +851,13 @@ static hipError_t linear(const LinArgs& a, hipStream_t s) {
     launch_wide(a, s);
   } else if (a.M <= 128) {
     launch_skinny<EPI>(a, s);
-  } else if ((size_t)((a.N + GemmBig::BN - 1) / GemmBig::BN) * ((a.M + GemmBig::BM - 1) / GemmBig::BM) >= 256) {
-    launch_gemm<EPI, GemmBig>(a, s);
-  } else if (a.K >= 3072) {
-    launch_gemm<EPI, GemmMidDeep>(a, s);
   } else {
-    launch_gemm<EPI, GemmMid>(a, s);
+    switch (gemm_tile(a.M, a.N)) {
+      case kGemmWide: launch_gemm<EPI, GemmWide>(a, s); break;
+      case kGemmTall: launch_gemm<EPI, GemmTall>(a, s); break;
+      case kGemmPair: launch_gemm<EPI, GemmPair>(a, s); break;
+      default: launch_gemm<EPI, GemmSmall>(a, s); break;
+    }
   }
   return hipGetLastError();
 }

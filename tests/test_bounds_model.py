@@ -409,6 +409,39 @@ def test_model_kernel_indexing(d, vocab, rows):
     assert 3 * 512 + 63 * 8 + 8 >= 2048         # the four chunks cover d = 2048
 
 
+@pytest.mark.parametrize("BM,BN,NS,WAVES_M,WAVES_N", [(128, 256, 3, 2, 4), (128, 128, 4, 2, 4), (128, 128, 2, 2, 2),
+                                                        (64, 64, 4, 2, 2)])
+def test_gemm_stage_layout(BM, BN, NS, WAVES_M, WAVES_N):
+    """k_gemm's stage in LDS: the DMA instructions of the waves write every
+    16-byte slot of it once, from inside the tile's rows, and each operand
+    read (one lane address per operand, the second 32-wide step's slots those
+    of the first with bit 2 flipped, tiles of 16 rows at fixed offsets) finds
+    the chunk of its row and step."""
+    BK, CPR, RPI, R256 = 64, 8, 8, 2
+    NW = WAVES_M * WAVES_N
+    WM, WN = BM // WAVES_M, BN // WAVES_N
+    IA, IB, STAGE = BM // RPI // NW, BN // RPI // NW, (BM + BN) * BK
+    assert NS * STAGE * 2 <= 160 * 1024 and IA * RPI * NW == BM and IB * RPI * NW == BN
+    swz = lambda r: (r // R256) % CPR
+    slots = {}                                     # element offset of a 16-byte slot -> (operand, row, chunk)
+    for wave, lane in itertools.product(range(NW), range(64)):
+        for op, n, base in (("x", IA, 0), ("w", IB, BM * BK)):
+            for i in range(n):
+                r = (wave * n + i) * RPI + lane // CPR
+                dst = base + (wave * n + i) * 512 + lane * 8
+                assert dst not in slots and dst + 8 <= STAGE and r < (BM if op == "x" else BN)
+                slots[dst] = (op, r, (lane % CPR) ^ swz(r))
+    assert len(slots) == STAGE // 8
+    for wave, lane, ks in itertools.product(range(NW), range(64), range(2)):
+        wm, wn = wave % WAVES_M, wave // WAVES_M
+        l16, g = lane & 15, lane >> 4
+        sl = ((g ^ swz(l16)) << 3) ^ (ks << 5)
+        for i in range(WM // 16):
+            assert slots[(wm * WM + l16) * BK + sl + i * 16 * BK] == ("x", wm * WM + i * 16 + l16, ks * 4 + g)
+        for j in range(WN // 16):
+            assert slots[BM * BK + (wn * WN + l16) * BK + sl + j * 16 * BK] == ("w", wn * WN + j * 16 + l16, ks * 4 + g)
+
+
 def _ln_groups_rows(d, rows=5):
     """k_ln_rows: the (chunk, group) partial each active lane sums, as the
     ordered k list it reads; every row of a wave (and of the last, partial

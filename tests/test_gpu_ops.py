@@ -227,3 +227,24 @@ def test_self_attention_argument_errors():
         with pytest.raises(smem.SmemError) as e:
             smem.smem_self_attention(z(64, d), z(d), z(d), z(3 * d, d), H, 1, path=smem.SA_FUSED)
         assert e.value.code == smem.SMEM_EINVAL
+
+
+# One output row has the same bits whichever kernel computes it: the tiled
+# GEMM at every tile choice (wide, tall, pair, small), at row and column
+# remainders of the tiles, and at reductions whose last chunk is short or
+# whose chunks are 512 wide, against the few-row kernel on 64 of its rows.
+@pytest.mark.parametrize("M,N,K,epi", [
+    (129, 64, 64, smem.LIN_STORE), (192, 1000, 832, smem.LIN_GELU), (1000, 3072, 768, smem.LIN_STORE),
+    (520, 8192, 1088, smem.LIN_GELU), (2047, 2052, 320, smem.LIN_RESID), (8065, 772, 256, smem.LIN_RESID),
+    (1025, 4100, 4352, smem.LIN_STORE), (257, 516, 8192, smem.LIN_RESID), (136, 9001, 448, smem.LIN_F32)])
+def test_gemm_rows_bitwise_few_row_kernel(M, N, K, epi):
+    say("gemm rows", M, N, K, epi)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+    x, w, res = r(M, K), r(N, K), r(M, N) if epi == smem.LIN_RESID else None
+    y = smem.smem_linear(x, w, epi=epi, res=res)
+    for r0 in sorted({0, M // 2, M - 64}):
+        part = smem.smem_linear(x[r0:r0 + 64].clone(), w, epi=epi,
+                                res=None if res is None else res[r0:r0 + 64].clone())
+        assert torch.equal(y[r0:r0 + 64], part), (r0, int((y[r0:r0 + 64] != part).sum()))
