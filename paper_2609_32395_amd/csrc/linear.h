@@ -59,92 +59,142 @@ __host__ __device__ constexpr int lin_chunk(int K) { return 256 * ((K + 256 * 16
 // LayerNorm of a row of width d (d % 64 == 0, d <= 2048), eps 1e-5, with the
 // statistics summed in one fixed order, so the stand-alone kernel below and
 // the few-row map that normalizes its own x rows give the same bits.  The row
-// is cut as a linear map cuts K: chunks of 256, each of 32-wide steps, each
-// step of four 8-wide groups.  The partial of (chunk, group) adds its values
-// in ascending k; a chunk's four partials add as (g0 + g1) + (g2 + g3); the
-// chunk totals add in ascending chunk order from zero.  mean = total / d; the
-// second moment sums (x - mean)^2 the same way; rstd = 1 / sqrt(m2 / d + eps).
-__device__ __forceinline__ float ln_sum8(const u32x4& c, float s) {
-  float f[8];
-  Chunk<uint16_t>::unpack(c, f);
+// is cut as a linear map cuts K: chunks of 256, each of 32 pieces of 8 values
+// (16 bytes).  A piece adds its values in ascending order; a chunk adds its
+// pieces as a binary tree (ln_tree32; missing pieces of a short last chunk as
+// zeros); the chunk totals add in ascending order from zero.  mean = total / d; the second moment sums (x - mean)^2 the
+// same way; rstd = 1 / sqrt(m2 / d + eps), the hardware's (1 ulp).
+__device__ __forceinline__ void ln_unpack(const u32x4& c, float (&f)[8]) { Chunk<uint16_t>::unpack(c, f); }
+__device__ __forceinline__ float ln_piece(const float (&f)[8]) {
+  float s = f[0];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) s += f[e];
+  for (int e = 1; e < 8; ++e) s += f[e];
   return s;
 }
-__device__ __forceinline__ float ln_sq8(const u32x4& c, float mean, float s) {
-  float f[8];
-  Chunk<uint16_t>::unpack(c, f);
+// f becomes f - mean; returns the sum of the squares
+__device__ __forceinline__ float ln_centre(float (&f)[8], float mean) {
+  float s = 0.f;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const float t = f[e] - mean;
-    s += t * t;
+    f[e] -= mean;
+    s = __builtin_fmaf(f[e], f[e], s);
   }
   return s;
 }
-__device__ __forceinline__ float ln_rstd(float m2, int d) { return 1.f / sqrtf(m2 / d + 1e-5f); }
-__device__ __forceinline__ u32x4 ln_apply8(const u32x4& x, const u32x4& g, const u32x4& b, float mean, float rstd) {
-  float xf[8], gf[8], bf[8];
-  Chunk<uint16_t>::unpack(x, xf);
-  Chunk<uint16_t>::unpack(g, gf);
-  Chunk<uint16_t>::unpack(b, bf);
+// (x - mean) already in f: f * rstd * gain + bias, packed to bf16
+__device__ __forceinline__ u32x4 ln_scale(const float (&f)[8], const float (&g)[8], const float (&b)[8], float rstd) {
   uint32_t w[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const float y0 = (xf[2 * e] - mean) * rstd * gf[2 * e] + bf[2 * e];
-    const float y1 = (xf[2 * e + 1] - mean) * rstd * gf[2 * e + 1] + bf[2 * e + 1];
+    const float y0 = __builtin_fmaf(f[2 * e] * rstd, g[2 * e], b[2 * e]);
+    const float y1 = __builtin_fmaf(f[2 * e + 1] * rstd, g[2 * e + 1], b[2 * e + 1]);
     w[e] = (uint32_t)f32_to_bf16_bits(y0) | ((uint32_t)f32_to_bf16_bits(y1) << 16);
   }
   return u32x4{w[0], w[1], w[2], w[3]};
 }
-
-// Stand-alone LayerNorm (rows x[row * ldx .. + d) -> y[row * ldy ..)): a
-// row takes 4 n_chunks lanes, lane 4c + g holding group g of chunk c, and a
-// wave holds 64 / (4 n_chunks) rows (4 at d = 1024), so every lane sums; the
-// gain and bias are loaded with the row.
-__host__ __device__ constexpr int ln_rows_per_wave(int d) { return 64 / (4 * ((d / 32 + 7) / 8)); }
-
-__global__ void __launch_bounds__(64) k_ln_rows(const uint16_t* __restrict__ x, int ldx,
-                                                const uint16_t* __restrict__ g, const uint16_t* __restrict__ b,
-                                                uint16_t* __restrict__ y, int ldy, int rows, int d) {
-  const int KS = d / 32, NC = (KS + 7) / 8, LPR = 4 * NC, R = 64 / LPR;
-  const int lane = threadIdx.x, rl = lane / LPR, base = rl * LPR, l = lane - base;
-  const int row = blockIdx.x * R + rl;
-  if (rl >= R || row >= rows) return;
-  const int c = l >> 2, k0 = 256 * c + 8 * (l & 3);
-  const int nt = min(8, KS - 8 * c);
-  const uint16_t* xr = x + (size_t)row * ldx + k0;
-  u32x4 v[8], gv[8], bv[8];
+// The tree over a chunk's 32 pieces, a piece per lane of a half-wave (or per
+// lane under an exclusive or of the index): partners 16, 8, 7, 3 and 1 apart
+// by exclusive or, each one exchange of the lanes.  Every lane gets the total.
+template <int CTRL>
+__device__ __forceinline__ float dpp_of(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+constexpr int kXor8 = 0x128, kXor7 = 0x141, kXor3 = 0x1B, kXor1 = 0xB1;   // row_ror:8, row_half_mirror, quad_perm
+__device__ __forceinline__ float add_swap16(float x, float y) {  // lanes 0-15: x of both, lanes 16-31: y of both
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float ln_tree32(float x) {
+  x = add_swap16(x, x);
+  x += dpp_of<kXor8>(x);
+  x += dpp_of<kXor7>(x);
+  x += dpp_of<kXor3>(x);
+  return x + dpp_of<kXor1>(x);
+}
+// The same tree for R rows at once, each level handing half of the rows to
+// each half of its lanes: lane s of a half-wave ends up with row (s >> 2) /
+// (8 / R) (bit 4 of s the row's highest).
+template <int R>
+__device__ __forceinline__ float ln_tree_rows(const float (&t)[R], int s) {
+  static_assert(R == 4 || R == 8, "two or three levels hand rows on");
+  float u[R / 2];
 #pragma unroll
-  for (int t = 0; t < 8; ++t)
-    if (t < nt) v[t] = *(const u32x4*)(xr + 32 * t);
+  for (int i = 0; i < R / 2; ++i) u[i] = add_swap16(t[i], t[i + R / 2]);
+  auto pick = [&](float x, float y, int bit) { return (s & bit) ? y : x; };
+  float v[R / 4];
 #pragma unroll
-  for (int t = 0; t < 8; ++t)
-    if (t < nt) {
-      gv[t] = *(const u32x4*)(g + k0 + 32 * t);
-      bv[t] = *(const u32x4*)(b + k0 + 32 * t);
+  for (int i = 0; i < R / 4; ++i)
+    v[i] = pick(u[i] + dpp_of<kXor8>(u[i]), u[i + R / 4] + dpp_of<kXor8>(u[i + R / 4]), 8);
+  float x = v[0] + dpp_of<kXor7>(v[0]);
+  if constexpr (R == 8) x = pick(x, v[1] + dpp_of<kXor7>(v[1]), 4);
+  x += dpp_of<kXor3>(x);
+  return x + dpp_of<kXor1>(x);
+}
+// The tree where a lane holds pieces 4 t + g in u[t] (g = lane / 16 of an MFMA
+// operand): its first two levels are between registers.
+__device__ __forceinline__ float ln_tree_operand(const float (&u)[8]) {
+  const float w0 = (u[0] + u[4]) + (u[2] + u[6]), w1 = (u[1] + u[5]) + (u[3] + u[7]);
+  const float v = w0 + __shfl_xor(w1, 48);
+  const float z = v + __shfl_xor(v, 48);
+  return z + __shfl_xor(z, 16);
+}
+__device__ __forceinline__ float ln_rstd(float m2, int d) { return __builtin_amdgcn_rsqf(m2 / d + 1e-5f); }
+
+// Stand-alone LayerNorm (rows x[row * ldx .. + d) -> y[row * ldy ..)): one
+// wave per row, a half-wave per chunk, every load and store 512 contiguous
+// bytes of the row per half-wave.
+__global__ void __launch_bounds__(256) k_ln_rows(const uint16_t* __restrict__ x, int ldx,
+                                                 const uint16_t* __restrict__ g, const uint16_t* __restrict__ b,
+                                                 uint16_t* __restrict__ y, int ldy, int rows, int d) {
+  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  const int NC = (d + 255) / 256, half = lane >> 5, k0 = half * 256 + (lane & 31) * 8;
+  const uint16_t* xr = x + (size_t)row * ldx;
+  float f[4][8];
+  u32x4 gv[4], bv[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (k0 + 512 * i < d) v = *(const u32x4*)(xr + k0 + 512 * i);
+    ln_unpack(v, f[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (k0 + 512 * i < d) {
+      gv[i] = *(const u32x4*)(g + k0 + 512 * i);
+      bv[i] = *(const u32x4*)(b + k0 + 512 * i);
     }
-  float s = 0.f;
+  auto total = [&](const float (&t)[4]) {
+    float s = 0.f;
 #pragma unroll
-  for (int t = 0; t < 8; ++t)
-    if (t < nt) s = ln_sum8(v[t], s);
-  s += __shfl_xor(s, 1);
-  s += __shfl_xor(s, 2);
-  float tot = 0.f;
-  for (int q = 0; q < NC; ++q) tot += __shfl(s, base + 4 * q);
-  const float mean = tot / d;
-  float m2 = 0.f;
+    for (int c = 0; c < 8; ++c)
+      if (c < NC) s += __shfl(t[c >> 1], (c & 1) * 32);
+    return s;
+  };
+  float t[4];
 #pragma unroll
-  for (int t = 0; t < 8; ++t)
-    if (t < nt) m2 = ln_sq8(v[t], mean, m2);
-  m2 += __shfl_xor(m2, 1);
-  m2 += __shfl_xor(m2, 2);
-  float tot2 = 0.f;
-  for (int q = 0; q < NC; ++q) tot2 += __shfl(m2, base + 4 * q);
-  const float rstd = ln_rstd(tot2, d);
-  uint16_t* yr = y + (size_t)row * ldy + k0;
+  for (int i = 0; i < 4; ++i) t[i] = 512 * i < d ? ln_tree32(ln_piece(f[i])) : 0.f;
+  const float mean = total(t) / d;
 #pragma unroll
-  for (int t = 0; t < 8; ++t)
-    if (t < nt) *(u32x4*)(yr + 32 * t) = ln_apply8(v[t], gv[t], bv[t], mean, rstd);
+  for (int i = 0; i < 4; ++i) {
+    const float q = ln_centre(f[i], mean);
+    t[i] = 512 * i < d ? ln_tree32(k0 + 512 * i < d ? q : 0.f) : 0.f;
+  }
+  const float rstd = ln_rstd(total(t), d);
+  uint16_t* yr = y + (size_t)row * ldy;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (k0 + 512 * i < d) {
+      float gf[8], bf[8];
+      ln_unpack(gv[i], gf);
+      ln_unpack(bv[i], bf);
+      *(u32x4*)(yr + k0 + 512 * i) = ln_scale(f[i], gf, bf, rstd);
+    }
+}
+
+inline void launch_ln(const uint16_t* x, int ldx, const uint16_t* g, const uint16_t* b, uint16_t* y, int ldy, int rows,
+                      int d, hipStream_t s) {
+  hipLaunchKernelGGL(k_ln_rows, dim3((rows + 3) / 4), dim3(256), 0, s, x, ldx, g, b, y, ldy, rows, d);
 }
 
 template <int EPI>
@@ -167,9 +217,10 @@ __device__ __forceinline__ void lin_store(const LinArgs& a, int m, int n, float 
 
 // Four consecutive outputs n .. n+3 of row m (n % 4 == 0; bf16 rows have
 // ldy % 4 == 0, so the four share one 8-byte word; a split's column groups
-// are multiples of 4 wide).  Columns >= N are dropped.
+// are multiples of 4 wide).  Columns >= N are dropped.  res: the residual's
+// word where it is at hand already.
 template <int EPI>
-__device__ __forceinline__ void lin_store4(const LinArgs& a, int m, int n, const f32x4& v) {
+__device__ __forceinline__ void lin_store4(const LinArgs& a, int m, int n, const f32x4& v, const u32x2* res = nullptr) {
   if constexpr (EPI == kLinF32) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
@@ -190,7 +241,7 @@ __device__ __forceinline__ void lin_store4(const LinArgs& a, int m, int n, const
       dst = a.y + (size_t)m * a.ldy + n;
     }
     if constexpr (EPI == kLinResid) {
-      const u32x2 r = *(const u32x2*)(a.res + (size_t)m * a.ldy + n);
+      const u32x2 r = res ? *res : *(const u32x2*)(a.res + (size_t)m * a.ldy + n);
       o[0] = v[0] + bf16_bits_to_f32(r.x & 0xffffu);
       o[1] = v[1] + bf16_bits_to_f32(r.x >> 16);
       o[2] = v[2] + bf16_bits_to_f32(r.y & 0xffffu);
@@ -231,89 +282,302 @@ __device__ __forceinline__ int xcd_order(int i, int T) {
 }
 __host__ __device__ constexpr int xcd_grid(int T) { return (T + 7) & ~7; }
 
-// Few rows (one or two blocks): the weights stream from HBM once and the
-// time is load latency, so the reduction chunks run side by side.  A
-// workgroup owns RT x 16 rows and G x 16 output columns and has one wave per
-// chunk; each wave keeps U steps of operands (RT tiles of x, G tiles of W) in
-// flight and leaves its chunk sums in LDS, where they are added in chunk
-// order.  Launch order puts the row tiles of one column group next to each
-// other on one XCD, so their W tiles are read from HBM once.
-// Dynamic LDS: n_chunks x RT x G x 1 KiB <= 64 KiB.
-template <int RT_, int G_, int U_>
-struct SkinnyCfg {
-  static constexpr int RT = RT_, G = G_, U = U_;
+// Few rows (one or two blocks, or a batch of decoded tokens): a workgroup
+// owns 16 rows and 16 G columns, and its waves take the reduction chunks side
+// by side, so the loads of the whole tile are in flight at once.  An MFMA
+// operand asks for 64 bytes of each of 16 rows; loaded like that from memory,
+// every instruction touches 16 lines by halves, and the time went into those
+// requests (16 rows x 4096 from L2 by 256 workgroups: 3.0 us against 0.65 for
+// 512 contiguous bytes per half-wave).  So a wave loads its 256-wide piece of
+// a 16-row tile as 8 instructions of two 512-byte rows, and passes it through
+// 8 KB of LDS of its own (no barrier) to turn it into the operand.  The
+// residual is asked for with the first loads.  Weights out of the caches, us
+// per call at 64 rows, before (fragments straight from memory) and now:
+// 1024 -> 1024 + residual 5.0 -> 3.7 (1.7 of it the launch), 4096 -> 1024 11.3
+// -> 7.2, 8192 -> 2048 27.6 -> 16.7; with the LayerNorm 1024 -> 1024 6.6 ->
+// 5.2, 1024 -> 3072 10.5 -> 8.1, 1024 -> 4096 + GELU 10.8 -> 8.2 (2.6 us of it
+// waits for the weights, 0.9 the statistics).
+//
+// LDS: row r of a piece is 32 slots of 16 bytes, chunk q in slot q ^ r, so
+// the 16 rows one operand read touches lie on distinct banks.
+struct FewTile {
+  static constexpr int BYTES = 8192;
+  // write: instruction i of a half-wave holds row r, chunk s = lane % 32
+  __device__ static int put(int r, int s) { return r * 512 + ((s ^ r) << 4); }
+  // operand of step t: lane (row l % 16, group l / 16) reads chunk 4 t + group
+  __device__ static int get(int lane, int t) {
+    return (lane & 15) * 512 + (((t * 4 + (lane >> 4)) ^ (lane & 15)) << 4);
+  }
 };
 
-template <int EPI, class C>
-__global__ void __launch_bounds__(1024) k_linear_skinny(LinArgs a, int row_tiles, int col_groups) {
-  constexpr int RT = C::RT, G = C::G, U = C::U, W16 = 16 * G;
-  extern __shared__ float part[];   // [n_chunks][16 RT][16 G]
+// The 8 instructions of a 16-row piece: rows row(2 i + lane / 32), chunk
+// lane % 32 of the nt * 4 valid ones from column k (a short last piece
+// re-reads its first chunk; its products are not formed).
+template <class Row>
+__device__ __forceinline__ void few_load(u32x4 (&v)[8], int lane, int k, int nt, Row row) {
+  const int s = lane & 31, q = s < 4 * nt ? s : 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = *(const u32x4*)(row(2 * i + (lane >> 5)) + k + q * 8);
+}
+__device__ __forceinline__ void few_put(uint8_t* tile, const u32x4 (&v)[8], int lane) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) *(u32x4*)(tile + FewTile::put(2 * i + (lane >> 5), lane & 31)) = v[i];
+}
+__device__ __forceinline__ void few_get(u32x4 (&o)[8], const uint8_t* tile, int lane) {
+#pragma unroll
+  for (int t = 0; t < 8; ++t) o[t] = *(const u32x4*)(tile + FewTile::get(lane, t));
+}
+// LDS operations of one wave run in order; this keeps the compiler to it.
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ void few_turn(u32x4 (&o)[8], uint8_t* tile, const u32x4 (&v)[8], int lane) {
+  wave_order();
+  few_put(tile, v, lane);
+  wave_order();
+  few_get(o, tile, lane);
+}
+// The steps that a short last piece does not have become zero operands.
+__device__ __forceinline__ void few_clip(u32x4 (&o)[8], int nt) {
+  if (nt == 8) return;
+#pragma unroll
+  for (int t = 1; t < 8; ++t)
+    if (t >= nt) o[t] = u32x4{0u, 0u, 0u, 0u};
+}
+__device__ __forceinline__ void few_mfma(f32x4& acc, const u32x4 (&B)[8], const u32x4 (&A)[8]) {
+#pragma unroll
+  for (int t = 0; t < 8; ++t) acc = mfma16(B[t], A[t], acc);
+}
+
+// The residual of the thread's first four outputs, asked for at the start.
+template <int EPI, int RT, int G>
+__device__ __forceinline__ u32x2 few_res(const LinArgs& a, int m0, int n0) {
+  if constexpr (EPI == kLinResid) {
+    const int q = threadIdx.x, m = m0 + q / (4 * G), n = n0 + (q % (4 * G)) * 4;
+    if (q < 64 * RT * G && m < a.M && n < a.N) return *(const u32x2*)(a.res + (size_t)m * a.ldy + n);
+  }
+  return u32x2{0u, 0u};
+}
+// The chunk sums in LDS ([n_chunks][16 RT][16 G]) added in chunk order, stored.
+template <int EPI, int RT, int G>
+__device__ __forceinline__ void few_finish(const LinArgs& a, const float* part, int NC, int m0, int n0,
+                                           const u32x2& res) {
+  for (int q = threadIdx.x; q < 64 * RT * G; q += blockDim.x) {
+    const int row = q / (4 * G), c0 = (q % (4 * G)) * 4;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    for (int c4 = 0; c4 < NC; c4 += 4) {
+      f32x4 p[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p[e] = *(const f32x4*)(part + (min(c4 + e, NC - 1) * 16 * RT + row) * 16 * G + c0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (c4 + e < NC) v += p[e];
+    }
+    const int m = m0 + row;
+    if (m < a.M) lin_store4<EPI>(a, m, n0 + c0, v, q < (int)blockDim.x ? &res : nullptr);
+  }
+}
+// A lane's sums of tile (row tile i, column tile j) of chunk c.
+template <int RT, int G>
+__device__ __forceinline__ void few_part(float* part, int c, int i, int j, const f32x4& acc, int lane) {
+  *(f32x4*)(part + ((c * RT + i) * 16 + (lane & 15)) * 16 * G + j * 16 + 4 * (lane >> 4)) = acc;
+}
+
+// RT row tiles by G column tiles.  LOOP: a wave takes the 8-step pieces of
+// chunks w, w + nw, .. (each chunk's in order), the next piece's loads issued
+// as soon as the registers are free; else one piece each.
+// Dynamic LDS: a tile of 8 KB per wave, then n_chunks x RT x G KB of chunk sums.
+template <int EPI, int RT, int G, int NW, bool LOOP>
+__global__ void __launch_bounds__(64 * NW) k_linear_few(LinArgs a, int row_tiles, int col_groups) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t few_lds[];
   const int pid = xcd_order(blockIdx.x, row_tiles * col_groups);
   if (pid < 0) return;
-  const int m0 = (pid % row_tiles) * 16 * RT, n0 = (pid / row_tiles) * W16;
-  const int lane = threadIdx.x & 63, c = threadIdx.x >> 6;       // wave c computes chunk c
-  const int kofs = (lane >> 4) * 8;
-  const int KS = a.K / 32, CS = lin_chunk(a.K) / 32, NC = (KS + CS - 1) / CS;
-  const uint16_t* ap[RT];
-  const uint16_t* bp[G];
+  const int m0 = (pid % row_tiles) * 16 * RT, n0 = (pid / row_tiles) * 16 * G;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nw = blockDim.x >> 6, KS = a.K / 32, CS = lin_chunk(a.K) / 32, NC = (KS + CS - 1) / CS;
+  uint8_t* tile = few_lds + w * FewTile::BYTES;
+  float* part = (float*)(few_lds + nw * FewTile::BYTES);
+  auto xrow = [&](int r) { return a.x + (size_t)min(m0 + r, a.M - 1) * a.ldx; };
+  auto wrow = [&](int r) { return lin_wrow(a, min(n0 + r, a.N - 1)); };
+  auto load_x = [&](u32x4 (&v)[8], int i, int st, int nt) {
+    few_load(v, lane, st * 32, nt, [&](int r) { return xrow(i * 16 + r); });
+  };
+  auto load_w = [&](u32x4 (&v)[8], int j, int st, int nt) {
+    few_load(v, lane, st * 32, nt, [&](int r) { return wrow(j * 16 + r); });
+  };
+  const u32x2 res = few_res<EPI, RT, G>(a, m0, n0);
+  u32x4 X[RT][8], W[G][8];
+  int c = w, st = c * CS;
+  auto steps = [&](int s0, int ch) { return min(8, min(KS, (ch + 1) * CS) - s0); };
+  if (c < NC) {
+    const int nt = steps(st, c);
 #pragma unroll
-  for (int i = 0; i < RT; ++i) ap[i] = a.x + (size_t)min(m0 + i * 16 + (lane & 15), a.M - 1) * a.ldx + kofs;
+    for (int i = 0; i < RT; ++i) load_x(X[i], i, st, nt);
 #pragma unroll
-  for (int j = 0; j < G; ++j) bp[j] = lin_wrow(a, min(n0 + j * 16 + (lane & 15), a.N - 1)) + kofs;
-  const int s0 = c * CS, s1 = min(KS, s0 + CS);
+    for (int j = 0; j < G; ++j) load_w(W[j], j, st, nt);
+  }
   f32x4 acc[RT][G];
 #pragma unroll
   for (int i = 0; i < RT; ++i)
 #pragma unroll
     for (int j = 0; j < G; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int u0 = s0; u0 < s1; u0 += U) {
-    u32x4 A[U][RT], B[U][G];
+  while (c < NC) {                       // (once, unless LOOP)
+    const int nt = steps(st, c);
+    int c2 = c, st2 = st + 8;            // the next piece
+    if (st2 >= min(KS, (c + 1) * CS)) {
+      c2 = c + nw;
+      st2 = c2 * CS;
+    }
+    const bool more = LOOP && c2 < NC;
+    const int nt2 = more ? steps(st2, c2) : 1;
+    u32x4 A[RT][8], B[8];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int st = min(u0 + u, s1 - 1) * 32;
-#pragma unroll
-      for (int j = 0; j < G; ++j) B[u][j] = *(const u32x4*)(bp[j] + st);
-#pragma unroll
-      for (int i = 0; i < RT; ++i) A[u][i] = *(const u32x4*)(ap[i] + st);
+    for (int i = 0; i < RT; ++i) {
+      few_turn(A[i], tile, X[i], lane);
+      if (more) load_x(X[i], i, st2, nt2);
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (u0 + u < s1) {
+    for (int j = 0; j < G; ++j) {
+      few_turn(B, tile, W[j], lane);
+      if (more) load_w(W[j], j, st2, nt2);
 #pragma unroll
-        for (int i = 0; i < RT; ++i)
+      for (int t = 0; t < 8; ++t)
+        if (t < nt) {
 #pragma unroll
-          for (int j = 0; j < G; ++j) acc[i][j] = mfma16(B[u][j], A[u][i], acc[i][j]);
-      }
+          for (int i = 0; i < RT; ++i) acc[i][j] = mfma16(B[t], A[i][t], acc[i][j]);
+        }
     }
+    if (!LOOP || c2 != c) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+          few_part<RT, G>(part, c, i, j, acc[i][j], lane);
+          acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    c = LOOP ? c2 : NC;
+    st = st2;
   }
-  float* pc = part + c * (256 * RT * G);
-#pragma unroll
-  for (int i = 0; i < RT; ++i)
-#pragma unroll
-    for (int j = 0; j < G; ++j)
-      *(f32x4*)(pc + (i * 16 + (lane & 15)) * W16 + j * 16 + 4 * (lane >> 4)) = acc[i][j];
   __syncthreads();
-  for (int q = threadIdx.x; q < 64 * RT * G; q += blockDim.x) {
-    const int row = q / (4 * G), c0 = (q % (4 * G)) * 4;
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    for (int ch = 0; ch < NC; ++ch) v += *(const f32x4*)(part + ch * (256 * RT * G) + row * W16 + c0);
-    const int m = m0 + row;
-    if (m < a.M) lin_store4<EPI>(a, m, n0 + c0, v);
-  }
+  few_finish<EPI, RT, G>(a, part, NC, m0, n0, res);
 }
 
-// Few rows with the LayerNorm fused (y = LN(x) W^T, K <= 2048, so every
-// chunk is 256 wide, 8 steps): each wave loads its chunk of the x rows whole,
-// the chunk partials of the row statistics meet in LDS in the fixed order of
-// the stand-alone kernel, and the rows are normalized in registers before the
-// MFMAs; the first U steps of W, issued with the x loads, are in flight
-// meanwhile, and each step's W registers are refilled with step t + U once
-// its MFMAs are issued.  The sums
-// are the same as k_linear_skinny's on LN(x) rows, so the output is bitwise
-// the unfused pair's.
+// The same with the LayerNorm fused (y = LN(x) W^T, K <= 2048, so every chunk
+// is 256 wide): WPC waves per chunk, each loading and normalizing 16 / WPC of
+// the rows and computing G / WPC of the column tiles; the chunk totals of the
+// row statistics meet in LDS in the stand-alone kernel's order, and the
+// normalized rows go into the chunk's tile.  A lane holds the same 8 columns
+// of all its rows, so it unpacks the gain and the bias once, and each value
+// once.  The weights, issued first, are in flight meanwhile.  The sums are
+// those of k_linear_few on LN(x) rows: bitwise the unfused pair's.
+// Dynamic LDS: n_chunks x WPC tiles, two planes [8][16] of statistics,
+// then n_chunks x G KB of chunk sums.
+template <int EPI, int G, int WPC>
+__global__ void __launch_bounds__(512) k_linear_few_ln(LinArgs a, int row_tiles, int col_groups) {
+  constexpr int GW = G / WPC, RI = 8 / WPC;              // column tiles, row pairs per wave
+  extern __shared__ __attribute__((aligned(16))) uint8_t few_lds[];
+  const int pid = xcd_order(blockIdx.x, row_tiles * col_groups);
+  if (pid < 0) return;
+  const int m0 = (pid % row_tiles) * 16, n0 = (pid / row_tiles) * 16 * G;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = w / WPC, h = w % WPC, half = lane >> 5, s = lane & 31;
+  const int KS = a.K / 32, NC = (KS + 7) / 8, nt = min(8, KS - 8 * c), k0 = c * 256;
+  uint8_t* xt = few_lds + c * WPC * FewTile::BYTES;      // the chunk's normalized rows
+  uint8_t* tile = few_lds + w * FewTile::BYTES;          // this wave's (h = 0: the rows' own, once they are read)
+  float* st0 = (float*)(few_lds + NC * WPC * FewTile::BYTES);
+  float* st1 = st0 + 128;
+  float* part = st1 + 128;
+  const u32x2 res = few_res<EPI, 1, G>(a, m0, n0);
+  const bool in = s < 4 * nt;
+  const int q = in ? s : 0;
+  u32x4 X[RI], W[GW][8], g16, b16;
+#pragma unroll
+  for (int i = 0; i < RI; ++i)
+    X[i] = *(const u32x4*)(a.x + (size_t)min(m0 + h * 2 * RI + 2 * i + half, a.M - 1) * a.ldx + k0 + q * 8);
+  g16 = *(const u32x4*)(a.lng + k0 + q * 8);
+  b16 = *(const u32x4*)(a.lnb + k0 + q * 8);
+  __builtin_amdgcn_sched_barrier(0);     // the rows, gain and bias are waited for without the weights
+#pragma unroll
+  for (int j = 0; j < GW; ++j)
+    few_load(W[j], lane, k0, nt, [&](int r) { return lin_wrow(a, min(n0 + (h * GW + j) * 16 + r, a.N - 1)); });
+  if (NC < 8)
+    for (int e = NC * 16 + threadIdx.x; e < 128; e += blockDim.x) st0[e] = st1[e] = 0.f;
+  // the row whose total the tree leaves in this lane (4 / (8 / RI) lanes hold it)
+  const int tr = h * 2 * RI + 2 * ((s >> 2) / (8 / RI)) + half;
+  float f[RI][8], z[RI];
+#pragma unroll
+  for (int i = 0; i < RI; ++i) {
+    ln_unpack(X[i], f[i]);
+    z[i] = in ? ln_piece(f[i]) : 0.f;
+  }
+  const float t0 = ln_tree_rows<RI>(z, s);
+  if ((s & 3) == 0) st0[c * 16 + tr] = t0;
+  // lane r finishes row r % 16 for the whole wave; its result is then fetched
+  // (chunks past the last are zeros)
+  auto total = [&](const float* st) {
+    float t = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) t += st[e * 16 + (lane & 15)];
+    return t;
+  };
+  auto fetch = [&](float (&o)[RI], float v) {
+#pragma unroll
+    for (int i = 0; i < RI; ++i) o[i] = __shfl(v, h * 2 * RI + 2 * i + half);
+  };
+  float rv[RI];
+  __syncthreads();
+  fetch(rv, total(st0) / a.K);
+#pragma unroll
+  for (int i = 0; i < RI; ++i) {
+    const float q2 = ln_centre(f[i], rv[i]);
+    z[i] = in ? q2 : 0.f;
+  }
+  const float t1 = ln_tree_rows<RI>(z, s);
+  if ((s & 3) == 0) st1[c * 16 + tr] = t1;
+  __syncthreads();
+  fetch(rv, ln_rstd(total(st1), a.K));
+  float gf[8], bf[8];
+  ln_unpack(g16, gf);
+  ln_unpack(b16, bf);
+#pragma unroll
+  for (int i = 0; i < RI; ++i)
+    *(u32x4*)(xt + FewTile::put(h * 2 * RI + 2 * i + half, s)) = ln_scale(f[i], gf, bf, rv[i]);
+  if constexpr (WPC > 1) __syncthreads();
+  else wave_order();
+  u32x4 A[8], B[2][8];
+  few_get(A, xt, lane);
+  few_clip(A, nt);
+  if constexpr (WPC > 1) __syncthreads();                // the rows are read; h = 0 reuses their tile
+  f32x4 acc[GW];
+  few_turn(B[0], tile, W[0], lane);
+#pragma unroll
+  for (int j = 0; j < GW; ++j) {
+    acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (j + 1 < GW) few_turn(B[(j + 1) & 1], tile, W[j + 1], lane);
+    few_clip(B[j & 1], nt);
+    few_mfma(acc[j], B[j & 1], A);
+  }
+#pragma unroll
+  for (int j = 0; j < GW; ++j) few_part<1, G>(part, c, 0, h * GW + j, acc[j], lane);
+  __syncthreads();
+  few_finish<EPI, 1, G>(a, part, NC, m0, n0, res);
+}
+
+// The same for wide rows (K > 1024) and many columns: RT x 16 rows and G x 16
+// columns per workgroup, one wave per chunk, x and W loaded as MFMA fragments
+// (a lane of step t holds piece 4 t + l / 16 of its row, so the statistics'
+// tree is partly between registers), U steps of W in flight.
 // Dynamic LDS: gain and bias (4 K bytes) and two statistics planes of
 // n_chunks x 16 RT floats, then, in the same space, n_chunks x RT x G KiB of
 // partial sums.
+template <int RT_, int G_, int U_>
+struct SkinnyCfg {
+  static constexpr int RT = RT_, G = G_, U = U_;
+};
+
 // An empty asm that claims to rewrite the packed x rows, so the compiler
 // unpacks them again where they are next used instead of keeping 8 floats
 // per register live across the statistics barriers.
@@ -368,12 +632,14 @@ __global__ void __launch_bounds__(512) k_linear_skinny_ln(LinArgs a, int row_til
   float mean[RT], rstd[RT];
 #pragma unroll
   for (int i = 0; i < RT; ++i) {
-    float v = 0.f;
+    float u[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
-      if (t < ns) v = ln_sum8(X[t][i], v);
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
+    for (int t = 0; t < 8; ++t) {
+      float f[8];
+      ln_unpack(X[t][i], f);
+      u[t] = t < ns ? ln_piece(f) : 0.f;
+    }
+    const float v = ln_tree_operand(u);
     if (lane < 16) st0[c * 16 * RT + i * 16 + lane] = v;
   }
   opaque(X);
@@ -383,12 +649,15 @@ __global__ void __launch_bounds__(512) k_linear_skinny_ln(LinArgs a, int row_til
     float tot = 0.f;
     for (int q = 0; q < NC; ++q) tot += st0[q * 16 * RT + i * 16 + (lane & 15)];
     mean[i] = tot / a.K;
-    float v = 0.f;
+    float u[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
-      if (t < ns) v = ln_sq8(X[t][i], mean[i], v);
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
+    for (int t = 0; t < 8; ++t) {
+      float f[8];
+      ln_unpack(X[t][i], f);
+      const float q = ln_centre(f, mean[i]);
+      u[t] = t < ns ? q : 0.f;
+    }
+    const float v = ln_tree_operand(u);
     if (lane < 16) st1[c * 16 * RT + i * 16 + lane] = v;
   }
   opaque(X);
@@ -402,9 +671,16 @@ __global__ void __launch_bounds__(512) k_linear_skinny_ln(LinArgs a, int row_til
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
     const int k = (s0 + min(t, ns - 1)) * 32 + kofs;
-    const u32x4 g8 = *(const u32x4*)(gb + k), b8 = *(const u32x4*)(gb + a.K + k);
+    float gf[8], bf[8];
+    ln_unpack(*(const u32x4*)(gb + k), gf);
+    ln_unpack(*(const u32x4*)(gb + a.K + k), bf);
 #pragma unroll
-    for (int i = 0; i < RT; ++i) X[t][i] = ln_apply8(X[t][i], g8, b8, mean[i], rstd[i]);
+    for (int i = 0; i < RT; ++i) {
+      float f[8];
+      ln_unpack(X[t][i], f);
+      ln_centre(f, mean[i]);
+      X[t][i] = ln_scale(f, gf, bf, rstd[i]);
+    }
   }
   __syncthreads();                       // gain, bias and statistics are read; part may be written
   f32x4 acc[RT][G];
@@ -441,34 +717,6 @@ __global__ void __launch_bounds__(512) k_linear_skinny_ln(LinArgs a, int row_til
   }
 }
 
-template <int EPI, class C>
-static void launch_skinny_cfg(const LinArgs& a, int nc, hipStream_t s) {
-  const int rt = (a.M + 16 * C::RT - 1) / (16 * C::RT), cg = (a.N + 16 * C::G - 1) / (16 * C::G);
-  hipLaunchKernelGGL((k_linear_skinny<EPI, C>), dim3(xcd_grid(rt * cg)), dim3(64 * nc), (size_t)nc * 1024 * C::RT * C::G, s,
-                     a, rt, cg);
-}
-
-// The widest tile that still gives at least 192 workgroups (one row tile
-// when M <= 16, where a second row tile is padding only): every workgroup
-// reads its rows of x and its columns of W whole, and reads issued at the
-// same time by several workgroups each cost close to a full read, so wider
-// tiles (fewer duplicated reads) win until too few workgroups remain to keep
-// the loads in flight (measured on the 64-row maps of the three model
-// scales).  Partial sums need n_chunks x RT x G KiB of LDS (at most 64).  All
-// tilings compute every output in the same order.
-template <int EPI>
-static void launch_skinny(const LinArgs& a, hipStream_t s) {
-  const int nc = (a.K + lin_chunk(a.K) - 1) / lin_chunk(a.K);
-  auto fits = [&](int rt, int g) {
-    const long wgs = (long)((a.M + 16 * rt - 1) / (16 * rt)) * ((a.N + 16 * g - 1) / (16 * g));
-    return wgs >= 192 && nc * rt * g <= 64 && (rt == 1 || a.M > 16);
-  };
-  if (fits(2, 4)) launch_skinny_cfg<EPI, SkinnyCfg<2, 4, 4>>(a, nc, s);
-  else if (fits(2, 2)) launch_skinny_cfg<EPI, SkinnyCfg<2, 2, 4>>(a, nc, s);
-  else if (fits(1, 2)) launch_skinny_cfg<EPI, SkinnyCfg<1, 2, 8>>(a, nc, s);
-  else launch_skinny_cfg<EPI, SkinnyCfg<1, 1, 8>>(a, nc, s);
-}
-
 inline size_t skinny_ln_lds(int nc, int rt, int g, int K) {
   return std::max((size_t)nc * 1024 * rt * g, (size_t)4 * K + (size_t)2 * nc * 16 * rt * 4);
 }
@@ -480,22 +728,79 @@ static void launch_skinny_ln_cfg(const LinArgs& a, int nc, hipStream_t s) {
                      skinny_ln_lds(nc, C::RT, C::G, a.K), s, a, rt, cg);
 }
 
-// The tiling rule of launch_skinny, with the LayerNorm's LDS counted; at
-// K <= 1024 one row tile of 2 column groups goes first (measured at 64 rows,
-// weights out of the last-level cache: 1024 -> 3072 10.4 against 11.0 us for
-// 2 x 2, 1024 -> 4096 10.5 against 11.2, 768 -> 3072 9.3 against 9.9).
+template <int EPI, int RT, int G, int NW, bool LOOP>
+static void launch_few_cfg(const LinArgs& a, int nc, hipStream_t s) {
+  const int rt = (a.M + 16 * RT - 1) / (16 * RT), cg = (a.N + 16 * G - 1) / (16 * G), nw = std::min(nc, NW);
+  hipLaunchKernelGGL((k_linear_few<EPI, RT, G, NW, LOOP>), dim3(xcd_grid(rt * cg)), dim3(64 * nw),
+                     (size_t)nw * FewTile::BYTES + (size_t)nc * RT * G * 1024, s, a, rt, cg);
+}
+// The tile (row tiles x column tiles of 16, waves) by size; us at 64 rows on
+// 1x1 / 2x1 / 2x2 / 2x4: 1024 -> 1024 3.7 / 4.4 / 5.7 / 8.6, 2048 -> 2048 6.9 /
+// 6.6 / 8.3 / 12.5, 1984 -> 7000 17.6 / 18.6 / 15.9 / 14.2, 2048 -> 50257 102 /
+// 100 / 89 / 85; 128 rows: 2048 -> 2048 10.9 / 10.1 / 8.3 / 12.2, 1024 -> 50257
+// 86 / 72 / 55 / 63.  Up to two 16 x 16 tiles per CU the smallest tile has the
+// most loads in flight; beyond that larger ones read x and W fewer times over,
+// and with K > 1024 and columns for 192 of them the widest.  9 to 16 chunks of
+// 256 (K <= 4096) take 16 waves with a chunk each (4096 -> 1024: 64 rows 7.3
+// on 1x1, 9.1 on 2x1; 128 rows 11.8 and 9.1), longer reductions 8 waves that
+// loop (8192 -> 2048 on 1x1 / 1x2: 32 rows 12.2 / 17.0, 64 rows 20.9 / 16.7).
 template <int EPI>
-static void launch_skinny_ln(const LinArgs& a, hipStream_t s) {
-  const int nc = (a.K + 255) / 256;
-  auto fits = [&](int rt, int g) {
-    const long wgs = (long)((a.M + 16 * rt - 1) / (16 * rt)) * ((a.N + 16 * g - 1) / (16 * g));
-    return wgs >= 192 && skinny_ln_lds(nc, rt, g, a.K) <= 65536 && (rt == 1 || a.M > 16);
+static void launch_few(const LinArgs& a, hipStream_t s) {
+  const int nc = (a.K + lin_chunk(a.K) - 1) / lin_chunk(a.K);
+  auto tiles = [&](int rt, int g) {
+    return (long)((a.M + 16 * rt - 1) / (16 * rt)) * ((a.N + 16 * g - 1) / (16 * g));
   };
-  if (a.K <= 1024 && fits(1, 2)) launch_skinny_ln_cfg<EPI, SkinnyCfg<1, 2, 8>>(a, nc, s);
-  else if (fits(2, 4)) launch_skinny_ln_cfg<EPI, SkinnyCfg<2, 4, 4>>(a, nc, s);
-  else if (fits(2, 2)) launch_skinny_ln_cfg<EPI, SkinnyCfg<2, 2, 8>>(a, nc, s);
-  else if (fits(1, 2)) launch_skinny_ln_cfg<EPI, SkinnyCfg<1, 2, 8>>(a, nc, s);
-  else launch_skinny_ln_cfg<EPI, SkinnyCfg<1, 1, 8>>(a, nc, s);
+  const long t = tiles(1, 1);
+  if (a.K > 4096) {
+    if (t > 256) launch_few_cfg<EPI, 1, 2, 8, true>(a, nc, s);
+    else launch_few_cfg<EPI, 1, 1, 8, true>(a, nc, s);
+  } else if (nc > 8) {
+    if (t > 256 && a.M > 16) launch_few_cfg<EPI, 2, 1, 16, false>(a, nc, s);
+    else launch_few_cfg<EPI, 1, 1, 16, false>(a, nc, s);
+  } else if (t <= 512 || a.M <= 16) {
+    launch_few_cfg<EPI, 1, 1, 8, false>(a, nc, s);
+  } else if (a.K > 1024 && tiles(2, 4) >= 192) {
+    launch_few_cfg<EPI, 2, 4, 8, false>(a, nc, s);
+  } else if (t >= 1024) {
+    launch_few_cfg<EPI, 2, 2, 8, false>(a, nc, s);
+  } else {
+    launch_few_cfg<EPI, 1, 1, 8, false>(a, nc, s);
+  }
+}
+
+template <int EPI, int G, int WPC>
+static void launch_few_ln_cfg(const LinArgs& a, int nc, hipStream_t s) {
+  const int rt = (a.M + 15) / 16, cg = (a.N + 16 * G - 1) / (16 * G);
+  hipLaunchKernelGGL((k_linear_few_ln<EPI, G, WPC>), dim3(xcd_grid(rt * cg)), dim3(64 * nc * WPC),
+                     (size_t)nc * WPC * FewTile::BYTES + 1024 + (size_t)nc * G * 1024, s, a, rt, cg);
+}
+// K <= 1024: as many columns per workgroup as leave about one workgroup per
+// CU, since each normalizes its 16 rows anew (us on 1 / 2 / 4 column tiles:
+// 64 rows 1024 -> 1024 5.2 / 5.4 / 7.1, 1024 -> 4096 10.4 / 8.4 / 8.2; 32 rows
+// 1024 -> 4096 7.2 / 6.3 / 8.2; 16 rows 5.7 / 6.2 / 8.3); past 1024 tiles of
+// 16 x 16 two column tiles again (128 rows 1024 -> 3072 13.2 / 10.5 / 13.8).
+// Wider rows with many columns keep 32-row tiles on MFMA-fragment loads
+// (64 rows, 2048 -> 8192: 20.8 against 25.7 us), which normalize half as often.
+template <int EPI>
+static void launch_few_ln(const LinArgs& a, hipStream_t s) {
+  const int nc = (a.K + 255) / 256;
+  const long rt = (a.M + 15) / 16, t = rt * ((a.N + 15) / 16);
+  if (nc <= 4) {
+    if (t <= 256) launch_few_ln_cfg<EPI, 1, 1>(a, nc, s);
+    else if (t <= 512 || t > 1024) launch_few_ln_cfg<EPI, 2, 2>(a, nc, s);
+    else launch_few_ln_cfg<EPI, 4, 2>(a, nc, s);
+    return;
+  }
+  if (t <= 512) {
+    launch_few_ln_cfg<EPI, 2, 1>(a, nc, s);
+    return;
+  }
+  auto fits = [&](int r, int g) {
+    const long wgs = (long)((a.M + 16 * r - 1) / (16 * r)) * ((a.N + 16 * g - 1) / (16 * g));
+    return wgs >= 192 && skinny_ln_lds(nc, r, g, a.K) <= 65536;
+  };
+  if (fits(2, 4)) launch_skinny_ln_cfg<EPI, SkinnyCfg<2, 4, 4>>(a, nc, s);
+  else launch_skinny_ln_cfg<EPI, SkinnyCfg<2, 2, 8>>(a, nc, s);
 }
 
 // Many rows: BM x BN tiles, WAVES_M x WAVES_N waves (each (BM/WAVES_M) x
@@ -834,13 +1139,11 @@ static hipError_t linear(const LinArgs& a, hipStream_t s) {
   if (a.lng) {
     if (!a.lnb || a.K > 2048 || a.ldx % 8) return hipErrorInvalidValue;
     if (a.M <= 128) {
-      launch_skinny_ln<EPI>(a, s);
+      launch_few_ln<EPI>(a, s);
       return hipGetLastError();
     }
     if (!a.lnout) return hipErrorInvalidValue;
-    const int rpw = ln_rows_per_wave(a.K);
-    hipLaunchKernelGGL(k_ln_rows, dim3((a.M + rpw - 1) / rpw), dim3(64), 0, s, a.x, a.ldx, a.lng, a.lnb, a.lnout, a.K,
-                       a.M, a.K);
+    launch_ln(a.x, a.ldx, a.lng, a.lnb, a.lnout, a.K, a.M, a.K, s);
     LinArgs n = a;
     n.x = a.lnout;
     n.ldx = a.K;
@@ -850,7 +1153,7 @@ static hipError_t linear(const LinArgs& a, hipStream_t s) {
   if (EPI == kLinF32 && wide_fits(a)) {
     launch_wide(a, s);
   } else if (a.M <= 128) {
-    launch_skinny<EPI>(a, s);
+    launch_few<EPI>(a, s);
   } else {
     switch (gemm_tile(a.M, a.N)) {
       case kGemmWide: launch_gemm<EPI, GemmWide>(a, s); break;

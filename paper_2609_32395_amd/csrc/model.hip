@@ -127,11 +127,14 @@ __global__ void __launch_bounds__(512) k_qkv_attn(QkvAttnArgs a) {
     if (worker) {
 #pragma unroll
       for (int i = 0; i < RT; ++i) {
-        float v = 0.f;
+        float u[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) v = ln_sum8(X[t][i], v);
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
+        for (int t = 0; t < 8; ++t) {
+          float f[8];
+          ln_unpack(X[t][i], f);
+          u[t] = ln_piece(f);
+        }
+        const float v = ln_tree_operand(u);
         if (lane < 16) st0[c * BT + r0 + i * 16 + lane] = v;
       }
       opaque(X);
@@ -143,11 +146,14 @@ __global__ void __launch_bounds__(512) k_qkv_attn(QkvAttnArgs a) {
         float tot = 0.f;
         for (int q = 0; q < NC; ++q) tot += st0[q * BT + r0 + i * 16 + (lane & 15)];
         mean[i] = tot / D;
-        float v = 0.f;
+        float u[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) v = ln_sq8(X[t][i], mean[i], v);
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
+        for (int t = 0; t < 8; ++t) {
+          float f[8];
+          ln_unpack(X[t][i], f);
+          u[t] = ln_centre(f, mean[i]);
+        }
+        const float v = ln_tree_operand(u);
         if (lane < 16) st1[c * BT + r0 + i * 16 + lane] = v;
       }
       opaque(X);
@@ -163,9 +169,16 @@ __global__ void __launch_bounds__(512) k_qkv_attn(QkvAttnArgs a) {
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
         const int k = c * 256 + t * 32 + kofs;
-        const u32x4 g8 = *(const u32x4*)(gb + k), b8 = *(const u32x4*)(gb + D + k);
+        float gf[8], bf[8];
+        ln_unpack(*(const u32x4*)(gb + k), gf);
+        ln_unpack(*(const u32x4*)(gb + D + k), bf);
 #pragma unroll
-        for (int i = 0; i < RT; ++i) X[t][i] = ln_apply8(X[t][i], g8, b8, mean[i], rstd[i]);
+        for (int i = 0; i < RT; ++i) {
+          float f[8];
+          ln_unpack(X[t][i], f);
+          ln_centre(f, mean[i]);
+          X[t][i] = ln_scale(f, gf, bf, rstd[i]);
+        }
       }
     }
   }
@@ -362,8 +375,7 @@ enum { R_LN1G, R_LN1B, R_QKV, R_O, R_LN2G, R_LN2B, R_Q, R_K, R_V, R_OC, R_LN3G, 
 
 hipError_t lnorm(const uint16_t* x, const uint16_t* g, const uint16_t* b, uint16_t* y, int rows, int d, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  const int rpw = ln_rows_per_wave(d);
-  hipLaunchKernelGGL(k_ln_rows, dim3((rows + rpw - 1) / rpw), dim3(64), 0, s, x, d, g, b, y, d, rows, d);
+  launch_ln(x, d, g, b, y, d, rows, d, s);
   return hipGetLastError();
 }
 

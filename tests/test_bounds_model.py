@@ -442,6 +442,62 @@ def test_gemm_stage_layout(BM, BN, NS, WAVES_M, WAVES_N):
             assert slots[BM * BK + (wn * WN + l16) * BK + sl + j * 16 * BK] == ("w", wn * WN + j * 16 + l16, ks * 4 + g)
 
 
+def test_few_row_tile_layout():
+    """The few-row maps' 16-row piece in a wave's LDS tile: the 8 loads'
+    writes fill 8 KB once, operand reads of step t find chunk 4 t + l / 16 of
+    row l % 16, and the 16 rows of one read lie in 16 different 16-byte
+    columns of the banks."""
+    put = lambda r, s: r * 512 + ((s ^ r) << 4)
+    get = lambda lane, t: (lane & 15) * 512 + (((t * 4 + (lane >> 4)) ^ (lane & 15)) << 4)
+    at = {}
+    for i, lane in itertools.product(range(8), range(64)):
+        r, s = 2 * i + (lane >> 5), lane & 31
+        assert 0 <= put(r, s) and put(r, s) + 16 <= 8192 and put(r, s) not in at
+        at[put(r, s)] = (r, s)
+    for t, lane in itertools.product(range(8), range(64)):
+        assert at[get(lane, t)] == (lane & 15, 4 * t + (lane >> 4))
+    for t, g in itertools.product(range(8), range(4)):
+        assert len({(get(g * 16 + r, t) >> 4) & 15 for r in range(16)}) == 16
+
+
+@pytest.mark.parametrize("R", [4, 8])
+def test_layernorm_tree_is_one_order(R):
+    """The statistics' tree over a chunk's 32 pieces adds in one order in its
+    three forms: a piece per lane, R rows at once, and pieces 4 t + g in the
+    registers of MFMA-operand lanes.  A sum is written as a nested pair whose
+    members are unordered (an addition commutes bit for bit)."""
+    add = lambda x, y: frozenset((x, y)) if x != y else (x, y)
+    lanes = range(32)
+    partner = {16: lambda s: s ^ 16, 8: lambda s: s ^ 8, 7: lambda s: s ^ 7, 3: lambda s: s ^ 3, 1: lambda s: s ^ 1}
+    x = {s: ("p", s) for s in lanes}
+    for k in (16, 8, 7, 3, 1):
+        x = {s: add(x[s], x[partner[k](s)]) for s in lanes}
+    assert len(set(x.values())) == 1
+    want = x[0]
+    # R rows: level 16 leaves lane s rows of its bit 4, level 8 of bit 3, level 7 (R = 8) of bit 2
+    row = lambda r, s: ("p", s) if r is None else (r, s)
+    t = [{s: row(r, s) for s in lanes} for r in range(R)]
+    u = [{s: add(t[i + (R // 2 if s & 16 else 0)][s], t[i + (R // 2 if s & 16 else 0)][s ^ 16]) for s in lanes}
+         for i in range(R // 2)]
+    v = [{s: add(u[i + (R // 4 if s & 8 else 0)][s], u[i + (R // 4 if s & 8 else 0)][s ^ 8]) for s in lanes}
+         for i in range(R // 4)]
+    y = {s: add(v[1 if R == 8 and s & 4 else 0][s], v[1 if R == 8 and s & 4 else 0][s ^ 7]) for s in lanes}
+    for k in (3, 1):
+        y = {s: add(y[s], y[partner[k](s)]) for s in lanes}
+    name = lambda tree, r: (frozenset if isinstance(tree, frozenset) else tuple)(
+        name(c, r) for c in tree) if isinstance(tree, frozenset) or isinstance(tree[0], (tuple, frozenset)) else (r, tree[1])
+    for s in lanes:
+        assert y[s] == name(want, (s >> 2) // (8 // R))
+    # operand lanes: group g holds pieces 4 t + g
+    o = {}
+    for g in range(4):
+        p = [("p", 4 * t_ + g) for t_ in range(8)]
+        o[g] = (add(add(p[0], p[4]), add(p[2], p[6])), add(add(p[1], p[5]), add(p[3], p[7])))
+    v1 = {g: add(o[g][0], o[g ^ 3][1]) for g in range(4)}
+    z = {g: add(v1[g], v1[g ^ 3]) for g in range(4)}
+    assert {add(z[g], z[g ^ 1]) for g in range(4)} == {want}
+
+
 def _ln_groups_rows(d, rows=5):
     """k_ln_rows: the (chunk, group) partial each active lane sums, as the
     ordered k list it reads; every row of a wave (and of the last, partial

@@ -248,3 +248,28 @@ def test_gemm_rows_bitwise_few_row_kernel(M, N, K, epi):
         part = smem.smem_linear(x[r0:r0 + 64].clone(), w, epi=epi,
                                 res=None if res is None else res[r0:r0 + 64].clone())
         assert torch.equal(y[r0:r0 + 64], part), (r0, int((y[r0:r0 + 64] != part).sum()))
+
+
+# The few-row maps (at most 128 rows) against the tiled GEMM (and, with the
+# LayerNorm, the stand-alone LayerNorm before it) on the same rows, bit for
+# bit: every tile of the few-row rules, row and column remainders, reductions
+# of one short chunk, with a short last chunk, of 9 to 16 chunks and longer.
+@pytest.mark.parametrize("M,N,K,ln,epi", [
+    (1, 36, 64, True, smem.LIN_STORE), (15, 100, 320, True, smem.LIN_GELU), (64, 1024, 1024, True, smem.LIN_STORE),
+    (33, 3076, 832, True, smem.LIN_STORE), (64, 4096, 1024, True, smem.LIN_GELU), (127, 3000, 768, True, smem.LIN_RESID),
+    (17, 2048, 1088, True, smem.LIN_STORE), (70, 6148, 1984, True, smem.LIN_STORE), (128, 5000, 2048, True, smem.LIN_F32),
+    (1, 4, 64, False, smem.LIN_STORE), (63, 1028, 1024, False, smem.LIN_RESID), (128, 2052, 2048, False, smem.LIN_RESID),
+    (49, 7001, 1984, False, smem.LIN_F32), (100, 4100, 448, False, smem.LIN_GELU), (31, 1024, 4096, False, smem.LIN_RESID),
+    (113, 772, 2368, False, smem.LIN_RESID), (64, 2048, 8192, False, smem.LIN_RESID), (9, 516, 4672, False, smem.LIN_STORE)])
+def test_few_rows_bitwise_many_rows(M, N, K, ln, epi):
+    say("few rows", M, N, K, ln, epi)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M * 3 + N + K)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+    big = 192
+    x, w, res = r(big, K) * 2 + 1, r(N, K), r(big, N) if epi == smem.LIN_RESID else None
+    lg, lb = (r(K), r(K)) if ln else (None, None)
+    few = smem.smem_linear(x[:M].clone(), w, lg, lb, epi, None if res is None else res[:M].clone())
+    many = smem.smem_linear(x, w, lg, lb, epi, res)
+    assert torch.isfinite(many.float()).all()
+    assert torch.equal(few, many[:M]), int((few != many[:M]).sum())
