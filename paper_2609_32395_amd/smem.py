@@ -17,6 +17,7 @@ class.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 
@@ -148,12 +149,28 @@ def check_status(code: int):
 
 
 def _i32(xs):
+    if not isinstance(xs, (bytes, bytearray)):
+        try:                             # whole numbers in range, copied in one go
+            a = array.array("i", xs)
+            if a:
+                return (ctypes.c_int32 * len(a)).from_buffer(a)
+        except (TypeError, OverflowError):
+            pass
     arr = (ctypes.c_int32 * max(1, len(xs)))(*[int(x) for x in xs])
     return arr
 
 
+# The current device's current stream, as torch.cuda.current_stream() gives it
+# without the Stream object around it (its lookups cost 4 us a call, more than
+# a launch).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_cur_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None and _cur_device is not None and torch.cuda.is_initialized():
+            return ctypes.c_void_p(_raw_stream(_cur_device()))
         return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     if isinstance(stream, torch.cuda.Stream):
         return ctypes.c_void_p(stream.cuda_stream)
@@ -174,6 +191,8 @@ def _dev(t, shape, dtype, name):
         return None
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
+    if t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous():
+        return ctypes.c_void_p(t.data_ptr())
     if t.device.type != "cuda":
         raise ValueError(f"{name} must be on the GPU")
     if t.dtype != dtype:

@@ -9,6 +9,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import smem_oracle as O
 from paper_2609_32395_amd import smem
@@ -185,3 +186,13 @@ def test_model_descriptor_and_weight_list():
         assert L.smem_model_bytes(ctypes.byref(bd)) == 0, field
     out = ctypes.c_void_p()
     assert L.smem_model_create(ctypes.byref(desc), None, None, 0, None, ctypes.byref(out)) == smem.SMEM_EINVAL
+
+
+@pytest.mark.parametrize("xs", [[1, 2, 3], (5,), [], range(4), [True, False], [1.7, 2], [2 ** 31 + 5, -1], "12", b"\x01\x02",
+                                np.array([1, 2], np.int64), np.array([1.5, 2.0]), [np.int32(7)], torch.tensor([4, 5])],
+                         ids=repr)
+def test_index_arrays_convert_as_int_of_each(xs):
+    """Index arguments become int32 arrays of int(x) of every entry (wrapped to
+    32 bits), one entry at least, whatever sequence they come in."""
+    want = [ctypes.c_int32(int(x)).value for x in xs] or [0]
+    assert list(smem._i32(xs)) == want
