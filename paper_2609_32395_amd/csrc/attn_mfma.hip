@@ -21,8 +21,9 @@
 // scalars, and P^T reaches the second product straight from the score
 // accumulators -- key tile 2c gives k-slots j<4 and tile 2c+1 gives j>=4, and
 // the A operand (transposed values) reads the same keys in the same slots.
-// The store keeps value planes transposed ([dh][b], keys contiguous) so that
-// operand is two contiguous 8-byte reads per lane.
+// The store keeps value planes transposed ([dh][b], keys contiguous) and the
+// key rows are ordered in LDS so that a lane's 8 slots are 8 consecutive keys:
+// that operand is one 16-byte read per lane.
 //
 // SMem+RoPE composite (ROPE = true; Section 3, "SMem composes with RoPE"):
 // queries and keys take rotary phases, values never do.  Inside a block the
@@ -319,19 +320,12 @@ __device__ __forceinline__ void prefill_body(const ReaderArgs& a, PrefillLds<DH,
     uint32_t src[R::IPW];
 #pragma unroll
     for (int i = 0; i < R::IPW; ++i) {
-      const int byte = (wave * R::IPW + i) * 1024 + lane * 16;
-      if (byte < R::KBYTES) {
-        const int r = byte / R::KRB, sl = (byte % R::KRB) >> 4;
-        src[i] = r * R::KRB + ((sl ^ R::kswz(r)) << 4);
-      } else {
-        const int vb = byte - R::KBYTES, d = vb >> 7, sl = (vb & 127) >> 4;
-        src[i] = R::KBYTES + d * 128 + ((sl ^ R::vswz(d)) << 4);
-      }
+      src[i] = R::source((wave * R::IPW + i) * 1024 + lane * 16);
     }
     const uint8_t* gpages = (const uint8_t*)a.pages;
     const uint32_t lds0 = (uint32_t)(uintptr_t)L.ring;
-    auto issue = [&](int pi, int stage) {
-      const uint8_t* t = gpages + page_head_offset(lpc[pi], h, a.H, BT, DH) * 2;
+    auto issue = [&](int page, int stage) {
+      const uint8_t* t = gpages + page_head_offset(page, h, a.H, BT, DH) * 2;
       const uint32_t d0 = lds0 + (uint32_t)(stage * R::TILE + wave * R::IPW * 1024);
 #pragma unroll
       for (int i = 0; i < R::IPW; ++i) dma16(t + src[i], __builtin_amdgcn_readfirstlane(d0 + i * 1024));
@@ -361,13 +355,16 @@ __device__ __forceinline__ void prefill_body(const ReaderArgs& a, PrefillLds<DH,
     wait_vm<0>();                          // query fragments and rotary rows, before any DMA is in flight
 #pragma unroll
     for (int k = 0; k < R::NS - 1; ++k)
-      if (p0 + k < p1) issue(p0 + k, k);
+      if (p0 + k < p1) issue(lpc[p0 + k], k);
     [[maybe_unused]] int split_end = p0 + pps;
     for (int pi = p0; pi < p1; ++pi) {
       const int k = pi - p0;
+      // the page that this step refills the ring with: the barrier's wait
+      // covers its lookup
+      const int next_page = lpc[min(pi + R::NS - 1, p1 - 1)];
       wait_pages<R::IPW>(min(R::NS - 2, p1 - 1 - pi));
       lds_barrier();                       // page pi is in LDS; every wave is done with page pi - 1
-      if (pi + R::NS - 1 < p1) issue(pi + R::NS - 1, (k + R::NS - 1) % R::NS);
+      if (pi + R::NS - 1 < p1) issue(next_page, (k + R::NS - 1) % R::NS);
       if constexpr (ROPE) {
         const int dlt = min(a.qblk[slot] - lbc[pi], a.rope_clip);
         if (dlt != turned) {
@@ -503,14 +500,7 @@ __global__ void __launch_bounds__(64 * 4 * QW) k_prefill_mfma_par(ReaderArgs a) 
   uint32_t src[P::IPW];
 #pragma unroll
   for (int i = 0; i < P::IPW; ++i) {
-    const int byte = (qw * P::IPW + i) * 1024 + lane * 16;
-    if (byte < R::KBYTES) {
-      const int r = byte / R::KRB, sl = (byte % R::KRB) >> 4;
-      src[i] = r * R::KRB + ((sl ^ R::kswz(r)) << 4);
-    } else {
-      const int vb = byte - R::KBYTES, d = vb >> 7, sl = (vb & 127) >> 4;
-      src[i] = R::KBYTES + d * 128 + ((sl ^ R::vswz(d)) << 4);
-    }
+    src[i] = R::source((qw * P::IPW + i) * 1024 + lane * 16);
   }
   const uint8_t* gpages = (const uint8_t*)a.pages;
   const uint32_t lds0 = (uint32_t)(uintptr_t)L + (uint32_t)(g * P::NSP * R::TILE + qw * P::IPW * 1024);

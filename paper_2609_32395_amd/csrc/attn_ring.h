@@ -95,8 +95,14 @@ __device__ __forceinline__ float qmax(float x) { return xor32_op_max(xor16_op_ma
 __device__ __forceinline__ float qsum(float x) { return xor32_op_sum(xor16_op_sum(x)); }
 
 
+// The key of a 64-key tile that a lane's score s[kt][i] belongs to: the two
+// 16-row score tiles of 32 keys interleave by fours (tile_row below), so the
+// lane's scores of tiles 2c and 2c + 1 are 8 consecutive keys.
+__device__ __forceinline__ int score_key(int kt, int i, int lane) {
+  return (kt >> 1) * 32 + (lane >> 4) * 8 + (kt & 1) * 4 + i;
+}
+
 // One online-softmax step over a 64-key tile for the lane's query.
-// valid(kt, i) says whether key kt*16 + 4*(lane/16) + i is visible.
 template <int DH, bool CAUSAL>
 __device__ __forceinline__ void online_step(floatx4 (&s)[4], float& m, float& l, floatx4 (&o)[DH / 16], int lane,
                                             int qrow, float scale_log2) {
@@ -111,52 +117,42 @@ __device__ __forceinline__ void online_step(floatx4 (&s)[4], float& m, float& l,
     for (int i = 0; i < 4; ++i) {
       float x = s[kt][i];
       if (CAUSAL) {
-        const int key = kt * 16 + (lane >> 4) * 4 + i;
-        if (key > qrow) x = -INFINITY;
+        if (score_key(kt, i, lane) > qrow) x = -INFINITY;
       }
       s[kt][i] = x;
       mx = fmaxf(mx, x);
     }
   }
-  mx = qmax(mx) * scale_log2;
-  // When no query of the wave raises its maximum, the rescale factor is
-  // exactly 1: l and o are left as they are (the same bits as multiplying).
-  if (__all(mx <= m)) {
-    float ps = 0.f;
+  // When no lane of the wave exceeds its query's maximum, no query raises it:
+  // the rescale factor is exactly 1, l and o stay as they are, and the four
+  // lanes of a query need not meet.  (The maximum itself, not a lazily moved
+  // reference: the largest weight is then exactly 1 in bf16, where a row of
+  // few keys would show its rounding.)
+  float alpha = 1.f;
+  if (!__all(mx * scale_log2 <= m)) {
+    const float mn = fmaxf(m, qmax(mx) * scale_log2);
+    // Without the causal mask every score is finite, so mn is finite and
+    // 2^(m - mn) = 2^-inf = 0 on the first tile: the guards are only needed
+    // when masked (-inf) scores can make mn = -inf.
+    alpha = (CAUSAL && m == -INFINITY) ? 0.f : exp2w(m - mn);
+    m = mn;
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt) {
+    for (int dt = 0; dt < DH / 16; ++dt) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float p = (CAUSAL && s[kt][i] == -INFINITY) ? 0.f : exp2w(__builtin_fmaf(s[kt][i], scale_log2, -m));
-        s[kt][i] = p;
-        ps += p;
-      }
+      for (int i = 0; i < 4; ++i) o[dt][i] *= alpha;
     }
-    l += ps;
-    return;
   }
-  const float mn = fmaxf(m, mx);
-  // Without the causal mask every score is finite, so mn is finite and
-  // 2^(m - mn) = 2^-inf = 0 on the first tile: the guards are only needed
-  // when masked (-inf) scores can make mn = -inf.
-  const float alpha = (CAUSAL && m == -INFINITY) ? 0.f : exp2w(m - mn);
   float ps = 0.f;
 #pragma unroll
   for (int kt = 0; kt < 4; ++kt) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float p = (CAUSAL && s[kt][i] == -INFINITY) ? 0.f : exp2w(__builtin_fmaf(s[kt][i], scale_log2, -mn));
+      const float p = (CAUSAL && s[kt][i] == -INFINITY) ? 0.f : exp2w(__builtin_fmaf(s[kt][i], scale_log2, -m));
       s[kt][i] = p;
       ps += p;
     }
   }
-  l = l * alpha + ps;
-  m = mn;
-#pragma unroll
-  for (int dt = 0; dt < DH / 16; ++dt) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[dt][i] *= alpha;
-  }
+  l = __builtin_fmaf(l, alpha, ps);
 }
 
 // ------------------------------------------------------------------ LDS tile layout
@@ -167,6 +163,9 @@ __device__ __forceinline__ void online_step(floatx4 (&s)[4], float& m, float& l,
 // permuted (key row r: slot = chunk ^ kswz(r); value row d: slot = chunk ^
 // vswz(d)), so the rows one MFMA operand read touches fall on distinct banks
 // (measured on gfx950: no bank conflicts for the key and value operand reads).
+// The key rows of each 32 are reordered by fours (key 8g + 4h + i in row 16h +
+// 4g + i): a lane's weights of two score tiles then belong to 8 consecutive
+// keys, and its value operand is one 16-byte read where it was two of 8.
 // Memory pages of the non-rotary prefill move global -> LDS by DMA
 // (global_load_lds_dwordx4, 16 bytes per lane) through a ring of NS page
 // stages, so NS - 1 pages are in flight while one is read and no register
@@ -193,10 +192,24 @@ struct PageRing {
   // bank probe of the score reads): r / 2 for 64-byte rows (r / 4 left them
   // 2-way conflicted), r / 2 for 128-byte rows, r for 256-byte rows.
   __device__ static constexpr int kswz(int r) { return (DH == 32 ? r / 2 : r / (256 / KRB)) % KCH; }
-  // the 16-row group (d >> 4) enters the value permutation so that the
-  // reads of rows d and d + 16 are never a fixed distance apart: merged into
-  // one read2 instruction, their two halves fell on the same banks
-  __device__ static constexpr int vswz(int d) { return ((d >> 1) ^ (d >> 4)) & 7; }
+  // value rows: 16 rows of 128 bytes per operand read, as the keys at d_h = 64
+  __device__ static constexpr int vswz(int d) { return (d >> 1) & 7; }
+  // LDS row of a key of the tile, and the key in an LDS row
+  __device__ static constexpr int tile_row(int key) {
+    return (key & ~31) + ((key >> 2) & 1) * 16 + ((key >> 3) & 3) * 4 + (key & 3);
+  }
+  __device__ static constexpr int row_key(int row) {
+    return (row & ~31) + ((row >> 2) & 3) * 8 + ((row >> 4) & 1) * 4 + (row & 3);
+  }
+  // Byte of the (page, head) tile in memory that LDS byte `byte` holds.
+  __device__ static int source(int byte) {
+    if (byte < KBYTES) {
+      const int r = byte / KRB, sl = (byte % KRB) >> 4;
+      return row_key(r) * KRB + ((sl ^ kswz(r)) << 4);
+    }
+    const int vb = byte - KBYTES, d = vb >> 7, sl = (vb & 127) >> 4;
+    return KBYTES + d * 128 + ((sl ^ vswz(d)) << 4);
+  }
 };
 
 // S^T for this wave's 16 queries against the 64 keys of a tile.
@@ -218,24 +231,20 @@ __device__ __forceinline__ void scores_ring(floatx4 (&s)[4], const uint8_t* tile
   }
 }
 
-// O^T += V^T P^T over the 64 keys of a tile: lane reads keys
-// 4 (l/16) + 16 q .. +3 of value row dt*16 + l%16, q = 0..3.
+// O^T += V^T P^T over the 64 keys of a tile: lane reads keys 8 (l/16) + 32 c
+// .. +7 of value row dt*16 + l%16, c = 0, 1.
 template <int DH>
 __device__ __forceinline__ void pv_ring(floatx4 (&o)[DH / 16], const uint8_t* tile, const floatx4 (&p)[4],
                                         int lane) {
   using R = PageRing<DH>;
   const bf16x8 p0 = pack_p(p[0], p[1]);
   const bf16x8 p1 = pack_p(p[2], p[3]);
-  const int g = lane >> 4;
+  const int off = R::KBYTES + (lane & 15) * 128 + (((lane >> 4) ^ R::vswz(lane & 15)) << 4);
+  static_assert(R::vswz(16) == 0, "one address serves every 16-row group");
 #pragma unroll
   for (int dt = 0; dt < DH / 16; ++dt) {
-    const int d = dt * 16 + (lane & 15);
-    const uint8_t* row = tile + R::KBYTES + d * 128 + (g & 1) * 8;
-    u32x2 x[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) x[q] = *(const u32x2*)(row + ((((g >> 1) + 2 * q) ^ R::vswz(d)) << 4));
-    const u32x4 a0 = u32x4{x[0].x, x[0].y, x[1].x, x[1].y};
-    const u32x4 a1 = u32x4{x[2].x, x[2].y, x[3].x, x[3].y};
+    const u32x4 a0 = *(const u32x4*)(tile + off + dt * 2048);
+    const u32x4 a1 = *(const u32x4*)(tile + (off ^ 64) + dt * 2048);
     o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), p0, o[dt], 0, 0, 0);
     o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), p1, o[dt], 0, 0, 0);
   }
@@ -278,7 +287,8 @@ __device__ __forceinline__ void intra_ring_store(uint8_t* tile, const uint16_t* 
         rope_turn<8>(x, tab + (size_t)row * DH, c8 * 4);
         kv = pack8(x);
       }
-      *(u32x4*)(tile + row * R::KRB + ((c8 ^ R::kswz(row)) << 4)) = kv;
+      const int lr = R::tile_row(row);
+      *(u32x4*)(tile + lr * R::KRB + ((c8 ^ R::kswz(lr)) << 4)) = kv;
     } else if (j < NJ) {
       const int pr = (j - NK) / CPR, c8 = (j - NK) % CPR;
       const uint32_t a4[4] = {ra[it].x, ra[it].y, ra[it].z, ra[it].w};

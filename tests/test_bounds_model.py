@@ -610,6 +610,46 @@ def test_gelu_erf_formula_in_source():
         assert np.max(np.abs(y[::50] - ref)) <= bound, dt
 
 
+@pytest.mark.parametrize("dh", [32, 64, 128])
+def test_attention_tile_key_order(dh):
+    """The 64-key tile in LDS with its key rows reordered by fours: the DMA's
+    source bytes are a permutation of the (page, head) tile; a lane's scores
+    s[kt][i] belong to the keys that the causal mask assumes, and the 8 slots
+    of its value operand c are the keys of its weights of score tiles 2c and
+    2c + 1, one 16-byte chunk of the transposed value row."""
+    BT, KRB, KB, KCH = 64, dh * 2, 64 * dh * 2, dh // 8
+    kswz = lambda r: ((r // 2) if dh == 32 else (r // (256 // KRB))) % KCH
+    vswz = lambda d: (d >> 1) & 7
+    tile_row = lambda k: (k & ~31) + ((k >> 2) & 1) * 16 + ((k >> 3) & 3) * 4 + (k & 3)
+    row_key = lambda r: (r & ~31) + ((r >> 2) & 3) * 8 + ((r >> 4) & 1) * 4 + (r & 3)
+    assert all(row_key(tile_row(k)) == k and tile_row(row_key(k)) == k for k in range(BT))
+
+    def source(byte):
+        if byte < KB:
+            r, sl = byte // KRB, (byte % KRB) >> 4
+            return row_key(r) * KRB + ((sl ^ kswz(r)) << 4)
+        d, sl = (byte - KB) >> 7, ((byte - KB) & 127) >> 4
+        return KB + d * 128 + ((sl ^ vswz(d)) << 4)
+
+    src = {b: source(b) for b in range(0, 2 * KB, 16)}
+    assert sorted(src.values()) == list(range(0, 2 * KB, 16))
+    key_of = lambda kt, i, lane: (kt >> 1) * 32 + (lane >> 4) * 8 + (kt & 1) * 4 + i
+    for lane in range(64):
+        g, l16 = lane >> 4, lane & 15
+        for kt, kk in itertools.product(range(4), range(dh // 32)):   # score operand: row kt*16 + l16, chunk kk*4 + g
+            r, c = kt * 16 + l16, kk * 4 + g
+            b = src[r * KRB + ((c ^ kswz(r)) << 4)]
+            assert b == row_key(r) * KRB + c * 16
+            # score row 4 g' + i of tile kt is the key of lane group g', value i
+            assert row_key(r) == key_of(kt, r % 4, (l16 // 4) * 16)
+        off = KB + l16 * 128 + ((g ^ vswz(l16)) << 4)
+        for dt, c in itertools.product(range(dh // 16), range(2)):
+            b = src[(off ^ (64 * c)) + dt * 2048]
+            first = (b - KB) % 128 // 2
+            assert (b - KB) // 128 == dt * 16 + l16
+            assert [first + j for j in range(8)] == [key_of(2 * c + j // 4, j % 4, lane) for j in range(8)]
+
+
 @pytest.mark.parametrize("dh,ns", [(32, 4), (64, 4), (128, 2)])
 def test_prefill_page_ring_indexing(dh, ns):
     """Non-rotary prefill's DMA page ring: every lane's source byte lies in
