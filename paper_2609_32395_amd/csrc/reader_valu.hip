@@ -58,16 +58,20 @@ __device__ __forceinline__ float wave_sum(float x) {
 // self-attention over its in-block cache): the page path is compiled out,
 // so the kernel holds fewer registers and more workgroups run at once; the
 // arithmetic of the split it runs is the same.
-template <typename T, int DH, int B, bool ROPE, bool MEM = true>
+// FOLD = true: a workgroup reads the splits of its (query, head) in turn and
+// folds them as the merge would, so there are no partials and no merge launch
+// (few, short splits: see launch_rv).
+template <typename T, int DH, int B, bool ROPE, bool MEM = true, bool FOLD = false>
 __global__ void __launch_bounds__(256) k_reader_valu(ReaderArgs a) {
   using C = RCfg<T, DH, B>;
   constexpr int E = C::E;
   // heads fastest: neighbouring workgroups stream the adjacent head tiles of
   // the same pages
-  const int h = blockIdx.x, split = blockIdx.y, qs = blockIdx.z;
+  const int h = blockIdx.x, qs = blockIdx.z;
   const int slot = qs / a.nq, t = qs % a.nq;
   const int n_read = a.n_read[slot], pps = a.pps[slot];
   const int nms = (n_read + pps - 1) / pps;
+  int split = FOLD ? 0 : (int)blockIdx.y;
   if (split > nms) return;  // whole workgroup
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -88,6 +92,8 @@ __global__ void __launch_bounds__(256) k_reader_valu(ReaderArgs a) {
 #pragma unroll
     for (int e = 0; e < E; ++e) qb[e] = qf[e];
   }
+  [[maybe_unused]] float fm = 0.f, fl = 0.f, fa = 0.f;   // FOLD: the splits so far, this thread's dimension
+  do {
   float m = -INFINITY, l = 0.f;
 
   if (MEM && split < nms) {
@@ -186,6 +192,10 @@ __global__ void __launch_bounds__(256) k_reader_valu(ReaderArgs a) {
     float acc2[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) acc2[e] = 0.f;
+    if constexpr (FOLD && ROPE) {          // the pages turned the query
+#pragma unroll
+      for (int e = 0; e < E; ++e) qf[e] = qb[e];
+    }
     if (a.null_kv != nullptr && wave == 0) {
       const T* nk = (const T*)a.null_kv + (size_t)h * DH + c * E;
       const T* nv = (const T*)a.null_kv + ((size_t)a.H + h) * DH + c * E;
@@ -282,7 +292,21 @@ __global__ void __launch_bounds__(256) k_reader_valu(ReaderArgs a) {
       L += wgt * wl[w];
       A += wgt * wacc[w][tid];
     }
-    if (nms == 0 && !a.intra_partial) {
+    if (FOLD && nms > 0) {
+      if (split == 0) {
+        fm = M;
+        fl = L;
+        fa = A;
+      } else {
+        const FoldScale fc = fold_scale(fm, M);
+        fl = fold_value(fl, fc, L);
+        fa = fold_value(fa, fc, A);
+      }
+      if (split == nms) {
+        const float inv = (fl > 0.f) ? 1.f / fl : 0.f;
+        ((T*)a.out)[((size_t)qs * a.H + h) * DH + tid] = from_f32<T>(fa * inv);
+      }
+    } else if (nms == 0 && !a.intra_partial) {
       const float o = (L > 0.f) ? A / L : 0.f;
       const T ov = from_f32<T>(o);
       ((T*)a.out)[((size_t)qs * a.H + h) * DH + tid] = ov;
@@ -298,6 +322,8 @@ __global__ void __launch_bounds__(256) k_reader_valu(ReaderArgs a) {
       if (tid == 0) { part[DH] = M; part[DH + 1] = L; }
     }
   }
+  if (FOLD) __syncthreads();               // the waves' states are read: the next split may write its own
+  } while (FOLD && split++ < nms);
 }
 
 // Merge the splits of one (query row, head) in split order by the running
@@ -361,6 +387,21 @@ static hipError_t launch_rv(const ReaderArgs& a, hipStream_t s) {
     if (ns > max_split) max_split = ns;
   }
   dim3 grid(a.H, max_split + 1, a.n_slots * a.nq);
+  // One workgroup per (query, head) folds one memory split with the null row
+  // and in-block keys, or two where a page is small (at most 4 loads per lane:
+  // blocks of 16, narrow heads): a phase more costs less than the merge's
+  // launch.  Decode of 64 sequences, us per call, folded against split + merge:
+  // 16 heads of 64 over 3 / 8 pages 16.6 / 29.4 against 20.3 / 34.7; two splits
+  // of 64-row pages 51.6 against 47.7 (16 pages), four 49.6 against 43.9.
+  using C = RCfg<T, DH, B>;
+  if (max_split > 0 && max_split <= (C::KLOADS + C::VLOADS <= 4 ? 2 : 1)) {
+    grid.y = 1;
+    if (a.rope != nullptr)
+      hipLaunchKernelGGL((k_reader_valu<T, DH, B, true, true, true>), grid, dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_reader_valu<T, DH, B, false, true, true>), grid, dim3(256), 0, s, a);
+    return hipGetLastError();
+  }
   if (a.rope != nullptr)
     hipLaunchKernelGGL((k_reader_valu<T, DH, B, true>), grid, dim3(256), 0, s, a);
   else if (max_split == 0)   // no slot reads a memory page

@@ -543,3 +543,52 @@ def test_device_copy_both_paths():
         assert torch.equal(dst.view(torch.int32), src.view(torch.int32))
     with pytest.raises(smem.SmemError):
         smem.smem_device_copy(torch.zeros(1000, device="cuda"), torch.zeros(1000, device="cuda"), via_lds=True)
+
+
+# A short read (one memory split, or two of blocks of 16) is folded by one
+# workgroup when every read of its launch is short, and split and merged when
+# a long read shares the launch: the same bits, with and without the null row,
+# in-block keys and rotary phases, in decode and in VALU prefill.
+@pytest.mark.parametrize("dtype,b,H,dh", [(torch.bfloat16, 64, 3, 32), (torch.bfloat16, 64, 2, 64),
+                                          (torch.bfloat16, 64, 2, 128), (torch.bfloat16, 16, 3, 32),
+                                          (torch.float32, 16, 2, 32), (torch.float32, 16, 2, 64), (torch.float32, 64, 1, 128)])
+@pytest.mark.parametrize("rope", [False, True])
+def test_short_reads_folded_bitwise_split(dtype, b, H, dh, rope):
+    say("short reads", dtype, b, H, dh, rope)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(b + H + dh)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda").to(dtype)
+    long, n = 70, 4
+    st = smem.Store(n, long, n * long, b, H, dh, dtype)
+    live = [1, 4, 8, long]                       # sequence 3's read is the long one
+    for s in range(n):
+        smem.smem_store_put_blocks(st, [s] * live[s], list(range(live[s])), r(live[s] * b, H, dh), r(live[s] * b, H, dh))
+    tab = smem.Rope(dh, 128, max_offset=3) if rope else None
+    null = r(2, H, dh)
+    pos = [0, b // 2, b - 1, 3]
+    q, kn, vn = r(n, H, dh), r(n, H, dh), r(n, H, dh)
+    kc, vc = r(n * b, H, dh), r(n * b, H, dh)
+
+    def decode(idx, own, nk):
+        rows = torch.tensor([s * b + i for s in idx for i in range(b)], device="cuda")
+        sel = torch.tensor(idx, device="cuda")
+        a = (idx, [live[s] for s in idx], [pos[s] for s in idx], q[sel].clone())
+        a += (kn[sel].clone(), vn[sel].clone(), kc[rows].clone(), vc[rows].clone()) if own else (None,) * 4
+        return smem.smem_reader_decode_rope(st, tab, *a, nk) if rope else smem.smem_reader_decode(st, *a, nk)
+
+    for own, nk in ((True, None), (False, null), (True, null)):
+        both = decode([0, 1, 2, 3], own, nk)
+        for s in range(3):
+            assert torch.equal(decode([s], own, nk)[0], both[s]), (own, nk is None, s)
+    if dtype == torch.bfloat16 and b == 64:
+        return                                   # prefill runs on the MFMA kernels there
+    Q, K, V = r(n * b, H, dh), r(n * b, H, dh), r(n * b, H, dh)
+
+    def prefill(idx):
+        rows = torch.tensor([s * b + i for s in idx for i in range(b)], device="cuda")
+        a = (idx, [live[s] for s in idx], Q[rows].clone(), K[rows].clone(), V[rows].clone(), null)
+        return smem.smem_reader_prefill_block_rope(st, tab, *a) if rope else smem.smem_reader_prefill_block(st, *a)
+
+    both = prefill([0, 1, 2, 3])
+    for s in range(3):
+        assert torch.equal(prefill([s]), both[s * b:(s + 1) * b]), s
