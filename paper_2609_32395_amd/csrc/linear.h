@@ -815,11 +815,14 @@ static void launch_few_ln(const LinArgs& a, hipStream_t s) {
 // next 32-wide step are read from LDS under the current step's MFMAs, and the
 // stage's one barrier sits between its two steps, with a step's products
 // ready to run behind it.  A chunk's first products start from a zero operand
-// and its sums join the totals under the last step's MFMAs.  Measured, us
-// (before: 128 x 128 tiles of 4 waves, one operand set): 8192 x 2048 x 8192
-// with the residual 285 -> 249 (1100 TFLOP/s; MFMA busy 56% of the cycles,
-// at the 1.92 GHz that this load leaves), 8192 x 8192 x 2048 with GELU 323 ->
-// 306, 8192 x 3072 x 1024 61 -> 57.
+// and its sums join the totals under the last step's MFMAs.  Where one
+// workgroup fills a CU, it takes tile after tile, and the next tile's first
+// stages are fetched while the last one's outputs are formed and stored.
+// Measured, us (before: 128 x 128 tiles of 4 waves, one operand set): 8192 x
+// 2048 x 8192 with the residual 285 -> 250 (1100 TFLOP/s; MFMA busy 56% of the
+// cycles, at the 1.92 GHz that this load leaves), 8192 x 8192 x 2048 with GELU
+// 321 -> 299, 8192 x 4096 x 1024 with GELU 90 -> 85, 8192 x 3072 x 1024 64 ->
+// 61, 4096 x 1024 x 1024 18.8 -> 14.6.
 template <int BM_, int BN_, int BK_, int NS_, int WAVES_M, int WAVES_N>
 struct GemmCfg {
   static constexpr int BM = BM_, BN = BN_, BK = BK_, NS = NS_;
@@ -830,6 +833,7 @@ struct GemmCfg {
   static constexpr int R256 = 256 / (BK * 2);        // rows per 256 bytes
   static constexpr int IA = BM / RPI / NW, IB = BN / RPI / NW;
   static constexpr int STAGE = (BM + BN) * BK;       // elements per stage
+  static constexpr int PER_CU = NS * STAGE * 2 <= 80 * 1024 ? 2 : 1;   // workgroups that fit a CU's LDS
   static_assert(IA * RPI * NW == BM && IB * RPI * NW == BN, "DMA rows must tile the stage");
   static_assert(NS >= 2 && NS <= 5, "ring depth");
   __device__ static constexpr int swz(int r) { return (r / R256) % CPR; }
@@ -849,27 +853,36 @@ __global__ void __launch_bounds__(C::NT, 2) k_gemm(LinArgs a, int tiles_m, int t
   constexpr int TM = C::TM, TN = C::TN, IA = C::IA, IB = C::IB, STAGE = C::STAGE, KSS = BK / 32;
   static_assert(KSS % 2 == 0, "the next stage's first step goes to operand set 0");
   __shared__ __attribute__((aligned(1024))) uint16_t lds[NS * STAGE];
-  // launch order -> tile: consecutive pids of one XCD, then groups of 8 row tiles
-  const int pid = xcd_order(blockIdx.x, tiles_m * tiles_n);
-  if (pid < 0) return;
-  const int per_group = 8 * tiles_n, g0 = (pid / per_group) * 8, gsz = min(tiles_m - g0, 8);
-  const int tm = g0 + (pid % per_group) % gsz, tn = (pid % per_group) / gsz;
-  const int n0 = tn * BN, m0 = tm * BM;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave % (BM / WM), wn = wave / (BM / WM);
   const int KT = a.K / BK, CT = lin_chunk(a.K) / BK;
+  const int T = tiles_m * tiles_n;
   const uint16_t* ga[IA];
   const uint16_t* gb[IB];
+  // Launch order -> tile: consecutive pids of one XCD, then groups of 8 row
+  // tiles.  A workgroup takes order index i, i + gridDim.x, .. (the grid is a
+  // multiple of 8, so all of them on its XCD).
+  int m0 = 0, n0 = 0;
+  auto place = [&](int i) {              // false: no tile at order index i
+    const int pid = i < xcd_grid(T) ? xcd_order(i, T) : -1;
+    if (pid < 0) return false;
+    const int per_group = 8 * tiles_n, g0 = (pid / per_group) * 8, gsz = min(tiles_m - g0, 8);
+    m0 = (g0 + (pid % per_group) % gsz) * BM;
+    n0 = ((pid % per_group) / gsz) * BN;
 #pragma unroll
-  for (int i = 0; i < IA; ++i) {
-    const int r = (wave * IA + i) * C::RPI + lane / C::CPR, c = (lane % C::CPR) ^ C::swz(r);
-    ga[i] = a.x + (size_t)min(m0 + r, a.M - 1) * a.ldx + c * 8;
-  }
+    for (int i = 0; i < IA; ++i) {
+      const int r = (wave * IA + i) * C::RPI + lane / C::CPR, c = (lane % C::CPR) ^ C::swz(r);
+      ga[i] = a.x + (size_t)min(m0 + r, a.M - 1) * a.ldx + c * 8;
+    }
 #pragma unroll
-  for (int i = 0; i < IB; ++i) {
-    const int r = (wave * IB + i) * C::RPI + lane / C::CPR, c = (lane % C::CPR) ^ C::swz(r);
-    gb[i] = lin_wrow(a, min(n0 + r, a.N - 1)) + c * 8;
-  }
+    for (int i = 0; i < IB; ++i) {
+      const int r = (wave * IB + i) * C::RPI + lane / C::CPR, c = (lane % C::CPR) ^ C::swz(r);
+      gb[i] = lin_wrow(a, min(n0 + r, a.N - 1)) + c * 8;
+    }
+    return true;
+  };
+  int order = blockIdx.x;
+  if (!place(order)) return;
   const uint32_t lbase = (uint32_t)(uintptr_t)lds;
   // the ring's stages in LDS bytes: the one read next, the one filled next
   uint32_t rd = 0, wr = 0;
@@ -889,10 +902,6 @@ __global__ void __launch_bounds__(C::NT, 2) k_gemm(LinArgs a, int tiles_m, int t
     wr = turn(wr);
   };
   f32x4 acc[TM][TN], tot[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   // operand registers, two sets: one 32-wide step's fragments are read from
   // LDS while the other's MFMAs run
   u32x4 A[2][TM], B[2][TN];
@@ -943,32 +952,49 @@ __global__ void __launch_bounds__(C::NT, 2) k_gemm(LinArgs a, int tiles_m, int t
       }
     }
   };
-  for (int p = 0; p < NS - 1 && p < KT; ++p) issue();
-  wait_stages<IA + IB>(min(NS - 2, KT - 1));
-  lds_barrier();
-  read(0, 0);
+  auto fill = [&]() {                    // the ring's first stages of a tile
+    for (int p = 0; p < NS - 1 && p < KT; ++p) issue();
+  };
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
-  int kt = 0;
-  for (const int full = KT - KT % CT; kt < full;) {
-    stage(yes, no, kt);
-    for (int e = kt + CT - 1; ++kt < e;) stage(no, no, kt);
-    stage(no, yes, kt++);
-  }
-  if (kt < KT) {                         // a last, shorter chunk
-    stage(yes, no, kt);
-    while (++kt < KT) stage(no, no, kt);
+  fill();
+  for (bool more = true; more;) {
+    wait_stages<IA + IB>(min(NS - 2, KT - 1));
+    lds_barrier();
+    read(0, 0);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) tot[i][j] += acc[i][j];
-  }
+      for (int j = 0; j < TN; ++j) tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int kt = 0;
+    for (const int full = KT - KT % CT; kt < full;) {
+      stage(yes, no, kt);
+      for (int e = kt + CT - 1; ++kt < e;) stage(no, no, kt);
+      stage(no, yes, kt++);
+    }
+    if (kt < KT) {                       // a last, shorter chunk
+      stage(yes, no, kt);
+      while (++kt < KT) stage(no, no, kt);
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int m = m0 + wm * WM + i * 16 + (lane & 15);
-    if (m < a.M) {
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) lin_store4<EPI>(a, m, n0 + wn * WN + j * 16 + 4 * (lane >> 4), tot[i][j]);
+        for (int j = 0; j < TN; ++j) tot[i][j] += acc[i][j];
+    }
+    // The next tile's first stages are fetched while this one is stored (the
+    // last stage's barrier left the ring free).
+    const int sm = m0, sn = n0;
+    more = C::PER_CU == 1 && place(order += gridDim.x);
+    if (more) {
+      wr = rd;
+      fill();
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int m = sm + wm * WM + i * 16 + (lane & 15);
+      if (m < a.M) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) lin_store4<EPI>(a, m, sn + wn * WN + j * 16 + 4 * (lane >> 4), tot[i][j]);
+      }
     }
   }
 }
@@ -1099,7 +1125,8 @@ static void launch_wide(const LinArgs& a, hipStream_t s) {
 template <int EPI, class C>
 static void launch_gemm(const LinArgs& a, hipStream_t s) {
   const int tm = (a.M + C::BM - 1) / C::BM, tn = (a.N + C::BN - 1) / C::BN;
-  hipLaunchKernelGGL((k_gemm<EPI, C>), dim3(xcd_grid(tm * tn)), dim3(C::NT), 0, s, a, tm, tn);
+  const int grid = C::PER_CU == 1 ? std::min(xcd_grid(tm * tn), 256) : xcd_grid(tm * tn);
+  hipLaunchKernelGGL((k_gemm<EPI, C>), dim3(grid), dim3(C::NT), 0, s, a, tm, tn);
 }
 
 // The tiles of a many-row map.  A wide tile moves fewer bytes from L2 into
@@ -1114,18 +1141,19 @@ enum GemmTile { kGemmWide, kGemmTall, kGemmPair, kGemmSmall };
 
 // The tile of an M x N map: the cheapest by rounds over the 256 CUs, a round
 // priced in rounds of the wide tile as measured (K 1024 .. 8192: 128 x 128
-// with 8 waves 0.56; 64 x 64 0.37 with one workgroup per CU and 0.45 with
-// two).  128 x 128 tiles that spill a little over one round go two to a CU
-// instead (0.85 up to 384 tiles: 520 x 8192 x 2048 33.9 us against 41.8 on
-// the wide tile).  us on wide / tall / pair / small tiles: 8192 x 1024 x 4096
-// 70.6 / - / 80.1 / -, 4096 x 3072 x 1024 36.4 / 33.6 / 35.5 / 44.2, 2048 x
-// 2048 x 2048 31.4 / 22.6 / 32.0 / 29.0, 1024 x 4096 x 1024 20.3 / 14.1 /
-// 19.1 / 17.0, 1024 x 1024 x 4096 50.3 / 33.4 / 52.7 / 19.5.
+// with 8 waves 0.61 to 0.69; 64 x 64 0.37 with one workgroup per CU and 0.45
+// with two).  128 x 128 tiles that spill a little over one round go two to a
+// CU instead (520 x 8192 x 2048, 320 of them: 33.9 us against 41.8 on the wide
+// tile; from 384 the wide tile is the faster).  us on wide / tall / pair /
+// small tiles: 8192 x 1024 x 4096 70 / 81 / 80 / 123, 5000 x 5000 x 1984 117 /
+// 124 / 119 / 155, 4096 x 3072 x 1024 36 / 34 / 36 / 45, 3072 x 2048 x 2048
+// 33 / 40 / 36 / 42, 2048 x 2048 x 2048 31 / 23 / 32 / 29, 1024 x 4096 x 1024
+// 20 / 14 / 19 / 17, 1024 x 1024 x 4096 50 / 33 / 53 / 20.
 inline GemmTile gemm_tile(int M, int N) {
   auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const long wide = tiles(128, 256), tall = tiles(128, 128), small = tiles(64, 64);
-  const long c_wide = (wide + 255) / 256 * 100, c_tall = (tall + 255) / 256 * 56;
-  const long c_pair = tall > 256 && tall <= 384 ? 85 : c_tall + 1;
+  const long c_wide = (wide + 255) / 256 * 100, c_tall = (tall + 255) / 256 * 63;
+  const long c_pair = tall > 256 && tall <= 352 ? 85 : c_tall + 1;
   const long c_small = small <= 256 ? 37 : (small + 511) / 512 * 45;
   const long best = std::min(std::min(c_wide, c_tall), std::min(c_pair, c_small));
   return best == c_small ? kGemmSmall : best == c_tall ? kGemmTall : best == c_pair ? kGemmPair : kGemmWide;

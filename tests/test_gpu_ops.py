@@ -236,6 +236,7 @@ def test_self_attention_argument_errors():
 @pytest.mark.parametrize("M,N,K,epi", [
     (129, 64, 64, smem.LIN_STORE), (192, 1000, 832, smem.LIN_GELU), (1000, 3072, 768, smem.LIN_STORE),
     (520, 8192, 1088, smem.LIN_GELU), (2047, 2052, 320, smem.LIN_RESID), (8065, 772, 256, smem.LIN_RESID),
+    (4100, 4100, 320, smem.LIN_GELU), (8193, 1200, 192, smem.LIN_RESID),
     (1025, 4100, 4352, smem.LIN_STORE), (257, 516, 8192, smem.LIN_RESID), (136, 9001, 448, smem.LIN_F32)])
 def test_gemm_rows_bitwise_few_row_kernel(M, N, K, epi):
     say("gemm rows", M, N, K, epi)
