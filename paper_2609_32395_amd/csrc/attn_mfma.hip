@@ -426,9 +426,10 @@ __device__ __forceinline__ void prefill_body(const ReaderArgs& a, PrefillLds<DH,
 // ------------------------------------------------------------------ few-pair prefill
 
 // Launches with few (query block, head) pairs and at most four memory splits
-// each.  A pair's 64 query rows go to 4/QW workgroups of 4 x QW waves (QW = 2,
-// the one launched: two workgroups of 32 rows, launched 8 indices apart so
-// both run on one XCD and the second fetch of each page hits its L2).
+// each.  A pair's 64 query rows go to 4/QW workgroups of 4 x QW waves (QW = 2:
+// two workgroups of 32 rows; QW = 1: four of 16, where they find a CU each),
+// launched 8 indices apart so all run on one XCD and the later fetches of each
+// page hit its L2.
 // Wave group g (QW waves of 16 rows each) reads memory split g through a DMA
 // ring of its own, so four page streams and four MFMA -> softmax -> MFMA
 // chains run on the CU at once; the groups step through their pages
@@ -645,7 +646,11 @@ static hipError_t launch_pre(const ReaderArgs& a, hipStream_t s) {
     constexpr int D = DH > 64 ? 64 : DH;                 // (no few-pair variant at d_h 128)
     if (a.rope || DH > 64 || max_split > ParLds<D, 4>::G) return hipErrorInvalidValue;
     const int n_pairs = a.n_slots * a.H;
-    hipLaunchKernelGGL((k_prefill_mfma_par<D, 2>), dim3(par_grid(n_pairs, 2)), dim3(512), 0, s, a);
+    // up to 64 pairs, four workgroups of 16 rows still run one per CU: us per
+    // call over 15 pages on QW 1 / 2: 32 heads of 32, 1 block 6.8 / 7.9, 4 blocks
+    // 12.8 / 9.0; 16 heads of 64, 1 block 8.4 / 9.8; 12 heads, 8 blocks 19.1 / 12.6
+    if (n_pairs <= 64) hipLaunchKernelGGL((k_prefill_mfma_par<D, 1>), dim3(par_grid(n_pairs, 1)), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_prefill_mfma_par<D, 2>), dim3(par_grid(n_pairs, 2)), dim3(512), 0, s, a);
     return hipGetLastError();
   }
   if (a.fuse) {

@@ -592,3 +592,29 @@ def test_short_reads_folded_bitwise_split(dtype, b, H, dh, rope):
     both = prefill([0, 1, 2, 3])
     for s in range(3):
         assert torch.equal(prefill([s]), both[s * b:(s + 1) * b]), s
+
+
+# Few-pair prefill gives a pair to four workgroups of 16 rows up to 64 pairs and
+# to two of 32 beyond: the same bits on both sides of that line.
+@pytest.mark.parametrize("dh", [32, 64])
+@pytest.mark.parametrize("with_null,with_intra", [(False, True), (True, False), (False, False)])
+def test_few_pair_row_split_bitwise(dh, with_null, with_intra):
+    say("few-pair row split", dh, with_null, with_intra)
+    b, H, live, dt = 64, 4, 16, torch.bfloat16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(dh)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda").to(dt)
+    st = smem.Store(1, live, live, b, H, dh, dt)
+    smem.smem_store_put_blocks(st, [0] * live, list(range(live)), r(live * b, H, dh), r(live * b, H, dh))
+    q, k, v, null = r(17 * b, H, dh), r(17 * b, H, dh), r(17 * b, H, dh), r(2, H, dh)
+
+    def run(lo, hi):                             # query block j of the sequence: j memory pages
+        cut = lambda x: x[lo * b:hi * b].clone()
+        return smem.smem_reader_prefill_block(st, [0] * (hi - lo), list(range(lo, hi)), cut(q), cut(k) if with_intra else None,
+                                              cut(v) if with_intra else None, null if with_null else None)
+
+    out = run(0, 17)                             # 68 pairs
+    assert torch.equal(run(0, 16), out[:16 * b])  # 64
+    assert torch.equal(run(1, 17), out[b:])
+    for j in range(17):
+        assert torch.equal(run(j, j + 1), out[j * b:(j + 1) * b]), j
