@@ -192,8 +192,13 @@ struct PageRing {
   // bank probe of the score reads): r / 2 for 64-byte rows (r / 4 left them
   // 2-way conflicted), r / 2 for 128-byte rows, r for 256-byte rows.
   __device__ static constexpr int kswz(int r) { return (DH == 32 ? r / 2 : r / (256 / KRB)) % KCH; }
-  // value rows: 16 rows of 128 bytes per operand read, as the keys at d_h = 64
-  __device__ static constexpr int vswz(int d) { return (d >> 1) & 7; }
+  // value rows: 16 rows of 128 bytes per operand read, as the keys at d_h = 64.
+  // At d_h = 128 the row group is added: a block's own values are written 16
+  // chunks of a row pair at a time, which d / 2 alone puts on two slots (8
+  // ways; encoder, 30 blocks of 20 heads 8.6 us against 8.9).  Below that one
+  // operand address for all row groups is worth more (d_h 64, 128 blocks of
+  // 12 heads: 9.2 us against 9.6).
+  __device__ static constexpr int vswz(int d) { return ((d >> 1) ^ (DH == 128 ? d >> 4 : 0)) & 7; }
   // LDS row of a key of the tile, and the key in an LDS row
   __device__ static constexpr int tile_row(int key) {
     return (key & ~31) + ((key >> 2) & 1) * 16 + ((key >> 3) & 3) * 4 + (key & 3);
@@ -240,11 +245,11 @@ __device__ __forceinline__ void pv_ring(floatx4 (&o)[DH / 16], const uint8_t* ti
   const bf16x8 p0 = pack_p(p[0], p[1]);
   const bf16x8 p1 = pack_p(p[2], p[3]);
   const int off = R::KBYTES + (lane & 15) * 128 + (((lane >> 4) ^ R::vswz(lane & 15)) << 4);
-  static_assert(R::vswz(16) == 0, "one address serves every 16-row group");
 #pragma unroll
   for (int dt = 0; dt < DH / 16; ++dt) {
-    const u32x4 a0 = *(const u32x4*)(tile + off + dt * 2048);
-    const u32x4 a1 = *(const u32x4*)(tile + (off ^ 64) + dt * 2048);
+    const int at = off ^ (R::vswz(dt * 16) << 4);
+    const u32x4 a0 = *(const u32x4*)(tile + at + dt * 2048);
+    const u32x4 a1 = *(const u32x4*)(tile + (at ^ 64) + dt * 2048);
     o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), p0, o[dt], 0, 0, 0);
     o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), p1, o[dt], 0, 0, 0);
   }

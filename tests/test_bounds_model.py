@@ -619,7 +619,7 @@ def test_attention_tile_key_order(dh):
     2c + 1, one 16-byte chunk of the transposed value row."""
     BT, KRB, KB, KCH = 64, dh * 2, 64 * dh * 2, dh // 8
     kswz = lambda r: ((r // 2) if dh == 32 else (r // (256 // KRB))) % KCH
-    vswz = lambda d: (d >> 1) & 7
+    vswz = lambda d: ((d >> 1) ^ (d >> 4 if dh == 128 else 0)) & 7
     tile_row = lambda k: (k & ~31) + ((k >> 2) & 1) * 16 + ((k >> 3) & 3) * 4 + (k & 3)
     row_key = lambda r: (r & ~31) + ((r >> 2) & 3) * 8 + ((r >> 4) & 1) * 4 + (r & 3)
     assert all(row_key(tile_row(k)) == k and tile_row(row_key(k)) == k for k in range(BT))
@@ -644,7 +644,7 @@ def test_attention_tile_key_order(dh):
             assert row_key(r) == key_of(kt, r % 4, (l16 // 4) * 16)
         off = KB + l16 * 128 + ((g ^ vswz(l16)) << 4)
         for dt, c in itertools.product(range(dh // 16), range(2)):
-            b = src[(off ^ (64 * c)) + dt * 2048]
+            b = src[(off ^ (vswz(16 * dt) << 4) ^ (64 * c)) + dt * 2048]
             first = (b - KB) % 128 // 2
             assert (b - KB) // 128 == dt * 16 + l16
             assert [first + j for j in range(8)] == [key_of(2 * c + j // 4, j % 4, lane) for j in range(8)]
