@@ -618,3 +618,26 @@ def test_few_pair_row_split_bitwise(dh, with_null, with_intra):
     assert torch.equal(run(1, 17), out[b:])
     for j in range(17):
         assert torch.equal(run(j, j + 1), out[j * b:(j + 1) * b]), j
+
+
+# At d_h 32 an encoder launch of at least 512 (block, head) tiles hands each XCD
+# a contiguous range of them: the same bits as launches below that, with
+# remainders of the 8 ranges and with the blocks' rows inserted into pages.
+@pytest.mark.parametrize("H,nb", [(8, 64), (7, 74), (12, 100), (6, 86)])
+@pytest.mark.parametrize("mask", [smem.MASK_BIDIR, smem.MASK_CAUSAL])
+def test_encoder_tile_ranges_bitwise(H, nb, mask):
+    say("encoder tile ranges", H, nb, mask)
+    b, dh = 64, 32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(H)
+    r = lambda: torch.randn(nb * b, H, dh, generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v = r(), r(), r()
+    st = smem.Store(1, nb, nb, b, H, dh)
+    out = smem.smem_encode_blocks(st, q, k, v, mask=mask, b=b, seq_ids=[0] * nb, block_idx=list(range(nb)))
+    half = H // 2                                # each call below has fewer than 512 tiles
+    for j0 in range(0, nb, 8):
+        for h in (slice(0, half), slice(half, H)):
+            cut = lambda x: x[j0 * b:(j0 + 8) * b, h].clone()
+            assert torch.equal(smem.smem_encode_blocks(None, cut(q), cut(k), cut(v), mask=mask, b=b), cut(out)), (j0, h)
+    _, K, V = smem.smem_store_export(st, 0)
+    assert torch.equal(K.reshape(out.shape), out) and torch.equal(V.reshape(out.shape), out)
