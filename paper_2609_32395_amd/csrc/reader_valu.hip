@@ -388,13 +388,17 @@ static hipError_t launch_rv(const ReaderArgs& a, hipStream_t s) {
   }
   dim3 grid(a.H, max_split + 1, a.n_slots * a.nq);
   // One workgroup per (query, head) folds one memory split with the null row
-  // and in-block keys, or two where a page is small (at most 4 loads per lane:
-  // blocks of 16, narrow heads): a phase more costs less than the merge's
-  // launch.  Decode of 64 sequences, us per call, folded against split + merge:
-  // 16 heads of 64 over 3 / 8 pages 16.6 / 29.4 against 20.3 / 34.7; two splits
-  // of 64-row pages 51.6 against 47.7 (16 pages), four 49.6 against 43.9.
+  // and in-block keys where a page is at most 32 loads per lane, or two splits
+  // (of 4 pages) of blocks of 16 with heads of 32: a phase more costs less than
+  // the merge's launch.  Us per call, folded against split + merge: decode of 64
+  // sequences, 16 heads of 64 over 3 / 8 pages 16.6 / 29.4 against 20.3 / 34.7,
+  // two splits of 64-row pages 51.6 against 47.7; prefill of a block of 16 over
+  // two splits, 4 heads of 32 6.0 against 6.4, 8 heads of 64 7.8 against 7.3;
+  // fp32 heads of 128, 64-row pages (64 loads per lane) 12.7 against 11.3, with
+  // rotary phases 41.6 against 32.3 (2 blocks of 8 heads).
   using C = RCfg<T, DH, B>;
-  if (max_split > 0 && max_split <= (C::KLOADS + C::VLOADS <= 4 ? 2 : 1)) {
+  constexpr int loads = C::KLOADS + C::VLOADS;
+  if (max_split > 0 && max_split <= (loads > 32 ? 0 : DH == 32 && loads <= 4 ? 2 : 1)) {
     grid.y = 1;
     if (a.rope != nullptr)
       hipLaunchKernelGGL((k_reader_valu<T, DH, B, true, true, true>), grid, dim3(256), 0, s, a);
