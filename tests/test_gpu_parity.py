@@ -641,3 +641,30 @@ def test_encoder_tile_ranges_bitwise(H, nb, mask):
             assert torch.equal(smem.smem_encode_blocks(None, cut(q), cut(k), cut(v), mask=mask, b=b), cut(out)), (j0, h)
     _, K, V = smem.smem_store_export(st, 0)
     assert torch.equal(K.reshape(out.shape), out) and torch.equal(V.reshape(out.shape), out)
+
+
+# Export and insert are compiled per (type, block rows, head width): every shape
+# gives back exactly the rows that were put, in block order, with head counts
+# and block counts that leave the workgroup order ragged.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("b", [16, 64])
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("H,nb", [(1, 1), (5, 7), (64, 3)])
+def test_put_export_every_shape_bitwise(dtype, b, dh, H, nb):
+    say("put and export", dtype, b, dh, H, nb)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(b + dh + H)
+    K, V = (torch.randn(nb * b, H, dh, generator=g, device="cuda").to(dtype) for _ in range(2))
+    st = smem.Store(2, nb + 2, nb, b, H, dh, dtype)
+    order = [(3 * i) % nb for i in range(nb)] if nb % 3 else [2, 0, 1][:nb]
+    for j in order[1:]:                          # one at a time, then the rest in one call
+        smem.smem_store_put_blocks(st, [1], [j], K[j * b:(j + 1) * b].clone(), V[j * b:(j + 1) * b].clone())
+    j = order[0]
+    smem.smem_store_put_blocks(st, [1], [j], K[j * b:(j + 1) * b].clone(), V[j * b:(j + 1) * b].clone())
+    idx, k, v = smem.smem_store_export(st, 1)
+    assert idx == list(range(nb)) and torch.equal(k, K) and torch.equal(v, V)
+    for j in range(nb):
+        smem.smem_delete_block(st, 1, j)
+    smem.smem_store_put_blocks(st, [0] * nb, list(range(nb)), K, V)
+    _, k, v = smem.smem_store_export(st, 0)
+    assert torch.equal(k, K) and torch.equal(v, V)
