@@ -61,8 +61,8 @@ inline int prefill_split_cap(int H) {
 // set-up; measured, a single block over 31 pages is faster split).
 // Otherwise one workgroup per split and a merge.  Either way the splits and
 // their fold are the same, so the choice never changes a result.
-// (Decode keeps the split launch and the merge: its one-query workgroups
-// stream a page per wave at a time, and folding them was measured slower.)
+// (Decode folds only short reads: its one-query workgroups stream a page per
+// wave at a time, and folding four splits was measured slower, see launch_rv.)
 #ifndef SMEM_FOLD_PAIRS
 #define SMEM_FOLD_PAIRS 512
 #endif
@@ -77,7 +77,7 @@ inline bool fold_in_workgroup(long n_pairs, int max_pages, int dh) {
 // A folding launch of at most kParPairs pairs at d_h <= 64 whose reads have
 // at most four memory splits runs the few-pair variant instead: one wave
 // group per split, the four read at once, each pair's query rows split over
-// two workgroups (same splits, same fold, same bits).
+// two or four workgroups (same splits, same fold, same bits).
 #ifndef SMEM_PAR_PAIRS
 #define SMEM_PAR_PAIRS 128
 #endif
