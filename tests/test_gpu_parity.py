@@ -545,8 +545,9 @@ def test_device_copy_both_paths():
         smem.smem_device_copy(torch.zeros(1000, device="cuda"), torch.zeros(1000, device="cuda"), via_lds=True)
 
 
-# A short read (one memory split, or two of blocks of 16) is folded by one
-# workgroup when every read of its launch is short, and split and merged when
+# A short read (one memory split, or two of blocks of 16 with heads of 32; not
+# fp32 heads of 128 in 64-row pages) is folded by one workgroup when every read
+# of its launch is short, and split and merged when
 # a long read shares the launch: the same bits, with and without the null row,
 # in-block keys and rotary phases, in decode and in VALU prefill.
 @pytest.mark.parametrize("dtype,b,H,dh", [(torch.bfloat16, 64, 3, 32), (torch.bfloat16, 64, 2, 64),
