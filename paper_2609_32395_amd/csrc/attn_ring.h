@@ -95,12 +95,11 @@ __device__ __forceinline__ float qmax(float x) { return xor32_op_max(xor16_op_ma
 __device__ __forceinline__ float qsum(float x) { return xor32_op_sum(xor16_op_sum(x)); }
 
 
-// The key of a 64-key tile that a lane's score s[kt][i] belongs to: the two
-// 16-row score tiles of 32 keys interleave by fours (tile_row below), so the
-// lane's scores of tiles 2c and 2c + 1 are 8 consecutive keys.
-__device__ __forceinline__ int score_key(int kt, int i, int lane) {
-  return (kt >> 1) * 32 + (lane >> 4) * 8 + (kt & 1) * 4 + i;
-}
+// The key of a 64-key tile that a lane's score s[kt][i] belongs to, less the
+// lane's own part 8 (lane / 16): the two 16-row score tiles of 32 keys
+// interleave by fours (tile_row below), so the lane's scores of tiles 2c and
+// 2c + 1 are 8 consecutive keys.
+__device__ constexpr int score_key(int kt, int i) { return (kt >> 1) * 32 + (kt & 1) * 4 + i; }
 
 // One online-softmax step over a 64-key tile for the lane's query.
 template <int DH, bool CAUSAL>
@@ -110,6 +109,7 @@ __device__ __forceinline__ void online_step(floatx4 (&s)[4], float& m, float& l,
   // positive and rounding is monotone, so this is the maximum of the scaled
   // scores); each weight is then 2^(s*scale - max) with the scale and the
   // shift in one fused multiply-add.
+  [[maybe_unused]] const int last = qrow - (lane >> 4) * 8;
   float mx = -INFINITY;
 #pragma unroll
   for (int kt = 0; kt < 4; ++kt) {
@@ -117,7 +117,7 @@ __device__ __forceinline__ void online_step(floatx4 (&s)[4], float& m, float& l,
     for (int i = 0; i < 4; ++i) {
       float x = s[kt][i];
       if (CAUSAL) {
-        if (score_key(kt, i, lane) > qrow) x = -INFINITY;
+        if (score_key(kt, i) > last) x = -INFINITY;
       }
       s[kt][i] = x;
       mx = fmaxf(mx, x);

@@ -35,3 +35,14 @@ def test_no_scratch_no_spills(src):
     for name, res in ks.items():
         assert res.get("ScratchSize [bytes/lane]", 0) == 0, (name, res)
         assert res.get("VGPRs Spill", 0) == 0 and res.get("SGPRs Spill", 0) == 0, (name, res)
+
+
+def test_encoder_waves_per_simd():
+    """Every encoder kernel leaves registers for four waves on a SIMD (four
+    workgroups on a CU): its workgroups wait for their own loads, and what the
+    others compute meanwhile is all that hides it."""
+    ks = _resource_remarks(os.path.join(B.CSRC, "attn_mfma.hip"))
+    enc = {n: r for n, r in ks.items() if "k_encoder_mfma" in n}
+    assert len(enc) == 12
+    for name, res in enc.items():
+        assert res["Occupancy [waves/SIMD]"] >= 4, (name, res)
