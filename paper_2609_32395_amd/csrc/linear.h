@@ -815,9 +815,13 @@ static void launch_few_ln(const LinArgs& a, hipStream_t s) {
 // next 32-wide step are read from LDS under the current step's MFMAs, and the
 // stage's one barrier sits between its two steps, with a step's products
 // ready to run behind it.  A chunk's first products start from a zero operand
-// and its sums join the totals under the last step's MFMAs.  Where one
-// workgroup fills a CU, it takes tile after tile, and the next tile's first
-// stages are fetched while the last one's outputs are formed and stored.
+// and its sums join the totals under the last step's MFMAs.  (A ring of two
+// stages waits for a stage where it is first read and keeps one operand set:
+// fetched ahead, operands have to land half a stage earlier.  us with and
+// without, 128 x 128 tiles: 8192 x 2304 x 768 45.8 and 43.1, 1536 x 8192 x 1024
+// 34.6 and 33.6, 1024 x 1024 x 4096 49.9 and 44.4.)  Where one workgroup fills
+// a CU, it takes tile after tile, and the next tile's first stages are fetched
+// while the last one's outputs are formed and stored.
 // Measured, us (before: 128 x 128 tiles of 4 waves, one operand set): 8192 x
 // 2048 x 8192 with the residual 285 -> 250 (1100 TFLOP/s; MFMA busy 56% of the
 // cycles, at the 1.92 GHz that this load leaves), 8192 x 8192 x 2048 with GELU
@@ -834,6 +838,8 @@ struct GemmCfg {
   static constexpr int IA = BM / RPI / NW, IB = BN / RPI / NW;
   static constexpr int STAGE = (BM + BN) * BK;       // elements per stage
   static constexpr int PER_CU = NS * STAGE * 2 <= 80 * 1024 ? 2 : 1;   // workgroups that fit a CU's LDS
+  static constexpr bool PLAIN = NS == 2;             // no operands fetched ahead of their stage
+  static_assert(!PLAIN || PER_CU == 2, "the next tile's fill needs the pipelined loop's last barrier");
   static_assert(IA * RPI * NW == BM && IB * RPI * NW == BN, "DMA rows must tile the stage");
   static_assert(NS >= 2 && NS <= 5, "ring depth");
   __device__ static constexpr int swz(int r) { return (r / R256) % CPR; }
@@ -961,24 +967,56 @@ __global__ void __launch_bounds__(C::NT, 2) k_gemm(LinArgs a, int tiles_m, int t
   for (bool more = true; more;) {
     wait_stages<IA + IB>(min(NS - 2, KT - 1));
     lds_barrier();
-    read(0, 0);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) tot[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     int kt = 0;
-    for (const int full = KT - KT % CT; kt < full;) {
-      stage(yes, no, kt);
-      for (int e = kt + CT - 1; ++kt < e;) stage(no, no, kt);
-      stage(no, yes, kt++);
-    }
-    if (kt < KT) {                       // a last, shorter chunk
-      stage(yes, no, kt);
-      while (++kt < KT) stage(no, no, kt);
+    if constexpr (C::PLAIN) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) tot[i][j] += acc[i][j];
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (; kt < KT; ++kt) {
+        if (kt > 0) {
+          wait_stages<IA + IB>(min(NS - 2, KT - 1 - kt));
+          lds_barrier();                 // stage kt is in LDS; every wave is done with stage kt - 1
+        }
+        if (kt + NS - 1 < KT) issue();
+#pragma unroll
+        for (int ks = 0; ks < KSS; ++ks) {
+          read(0, ks);
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = mfma16(B[0][j], A[0][i], acc[i][j]);
+        }
+        rd = turn(rd);
+        if ((kt + 1) % CT == 0 || kt + 1 == KT) {
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+              tot[i][j] += acc[i][j];
+              acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+      }
+    } else {
+      read(0, 0);
+      for (const int full = KT - KT % CT; kt < full;) {
+        stage(yes, no, kt);
+        for (int e = kt + CT - 1; ++kt < e;) stage(no, no, kt);
+        stage(no, yes, kt++);
+      }
+      if (kt < KT) {                     // a last, shorter chunk
+        stage(yes, no, kt);
+        while (++kt < KT) stage(no, no, kt);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) tot[i][j] += acc[i][j];
+      }
     }
     // The next tile's first stages are fetched while this one is stored (the
     // last stage's barrier left the ring free).
@@ -1137,26 +1175,47 @@ using GemmWide = GemmCfg<128, 256, 64, 3, 2, 4>;   // one workgroup of 8 waves p
 using GemmTall = GemmCfg<128, 128, 64, 4, 2, 4>;   // one of 8 waves per CU (128 KB)
 using GemmPair = GemmCfg<128, 128, 64, 2, 2, 2>;   // two of 4 waves per CU (64 KB each)
 using GemmSmall = GemmCfg<64, 64, 64, 4, 2, 2>;    // two of 4 waves per CU (64 KB each)
-enum GemmTile { kGemmWide, kGemmTall, kGemmPair, kGemmSmall };
+using GemmBrief = GemmCfg<64, 64, 64, 2, 2, 2>;    // four of 4 waves per CU (32 KB each): short reductions
+enum GemmTile { kGemmWide, kGemmTall, kGemmPair, kGemmSmall, kGemmBrief };
 
-// The tile of an M x N map: the cheapest by rounds over the 256 CUs, a round
-// priced in rounds of the wide tile as measured (K 1024 .. 8192: 128 x 128
-// with 8 waves 0.61 to 0.69; 64 x 64 0.37 with one workgroup per CU and 0.45
-// with two).  128 x 128 tiles that spill a little over one round go two to a
-// CU instead (520 x 8192 x 2048, 320 of them: 33.9 us against 41.8 on the wide
-// tile; from 384 the wide tile is the faster).  us on wide / tall / pair /
-// small tiles: 8192 x 1024 x 4096 70 / 81 / 80 / 123, 5000 x 5000 x 1984 117 /
-// 124 / 119 / 155, 4096 x 3072 x 1024 36 / 34 / 36 / 45, 3072 x 2048 x 2048
-// 33 / 40 / 36 / 42, 2048 x 2048 x 2048 31 / 23 / 32 / 29, 1024 x 4096 x 1024
-// 20 / 14 / 19 / 17, 1024 x 1024 x 4096 50 / 33 / 53 / 20.
-inline GemmTile gemm_tile(int M, int N) {
-  auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  const long wide = tiles(128, 256), tall = tiles(128, 128), small = tiles(64, 64);
-  const long c_wide = (wide + 255) / 256 * 100, c_tall = (tall + 255) / 256 * 63;
-  const long c_pair = tall > 256 && tall <= 352 ? 85 : c_tall + 1;
-  const long c_small = small <= 256 ? 37 : (small + 511) / 512 * 45;
-  const long best = std::min(std::min(c_wide, c_tall), std::min(c_pair, c_small));
-  return best == c_small ? kGemmSmall : best == c_tall ? kGemmTall : best == c_pair ? kGemmPair : kGemmWide;
+// The tile of an M x N x K map: the cheapest by rounds over the 256 CUs.  A
+// round of a tile is priced by what its workgroups take when j of them share a
+// CU, (step + step_more (j - 1)) per 64 columns of K plus base + base_more (j -
+// 1) for their start and end, in hundredths of a us: over 1994 measured maps (M
+// 129 .. 8192, N 64 .. 12001, K 64 .. 8192, every epilogue) the choice costs
+// 0.3% over the best tile on average, and more than 5% in one of a hundred.  A
+// wide tile moves the fewest bytes per product but starts slowest, so the price
+// has to know K.  us on wide / tall / pair / small / brief tiles: 320 x 8192 x
+// 320 10.5 / 7.5 / 7.9 / 7.5 / 6.5, 640 x 2048 x 512 13.5 / 9.3 / 10.7 / 6.8 /
+// 7.5, 2048 x 3072 x 256 11.5 / 12.8 / 10.9 / 11.8 / 10.8, 1024 x 3072 x 768
+// 16.2 / 11.3 / 12.8 / 12.6 / 10.7, 8192 x 2304 x 768 47.1 / 45.0 / 43.1 / 54.0
+// / 49.8, 640 x 8192 x 4096 58 / 73 / 66 / 78 / 98, 8192 x 8192 x 2048 283 /
+// 340 / 310 / 437 / 416.
+struct GemmPrice {
+  int bm, bn, per_cu, step, base, step_more, base_more;
+};
+constexpr GemmPrice kGemmPrice[] = {
+    {128, 256, 1, 76, 625, 0, 0},    // wide
+    {128, 128, 1, 47, 350, 0, 0},    // tall
+    {128, 128, 2, 62, 298, 30, 223}, // pair
+    {64, 64, 2, 22, 107, 14, 56},    // small
+    {64, 64, 4, 32, 68, 13, 61},     // brief
+};
+inline GemmTile gemm_tile(int M, int N, int K) {
+  int best = 0;
+  long least = 0;
+  for (int i = 0; i < 5; ++i) {
+    const GemmPrice& p = kGemmPrice[i];
+    const long tiles = (long)((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn);
+    auto round = [&](long j) { return (p.step + p.step_more * (j - 1)) * (K / 64) + p.base + p.base_more * (j - 1); };
+    const long full = tiles / (256 * p.per_cu), rest = tiles % (256 * p.per_cu);
+    const long price = full * round(p.per_cu) + (rest ? round((rest + 255) / 256) : 0);
+    if (i == 0 || price < least) {
+      least = price;
+      best = i;
+    }
+  }
+  return (GemmTile)best;
 }
 
 template <int EPI>
@@ -1183,11 +1242,12 @@ static hipError_t linear(const LinArgs& a, hipStream_t s) {
   } else if (a.M <= 128) {
     launch_few<EPI>(a, s);
   } else {
-    switch (gemm_tile(a.M, a.N)) {
+    switch (gemm_tile(a.M, a.N, a.K)) {
       case kGemmWide: launch_gemm<EPI, GemmWide>(a, s); break;
       case kGemmTall: launch_gemm<EPI, GemmTall>(a, s); break;
       case kGemmPair: launch_gemm<EPI, GemmPair>(a, s); break;
-      default: launch_gemm<EPI, GemmSmall>(a, s); break;
+      case kGemmSmall: launch_gemm<EPI, GemmSmall>(a, s); break;
+      default: launch_gemm<EPI, GemmBrief>(a, s); break;
     }
   }
   return hipGetLastError();

@@ -7,6 +7,7 @@ the ABI sizes for it.  It runs before any kernel change goes to a GPU: an
 access past a tensor's end is caught here, not as a memory fault."""
 import itertools
 import os
+import re
 
 import pytest
 
@@ -409,8 +410,53 @@ def test_model_kernel_indexing(d, vocab, rows):
     assert 3 * 512 + 63 * 8 + 8 >= 2048         # the four chunks cover d = 2048
 
 
+def _source(name):
+    return open(os.path.join(os.path.dirname(__file__), "..", "paper_2609_32395_amd", "csrc", name)).read()
+
+
+def _gemm_prices():
+    """kGemmPrice of linear.h: rows per tile, columns per tile, workgroups per
+    CU, step, base, step_more, base_more."""
+    body = re.search(r"kGemmPrice\[\] = \{(.*?)\};", _source("linear.h"), re.S).group(1)
+    return [tuple(int(x) for x in m.split(",")) for m in re.findall(r"\{([-0-9, ]+)\}", body)]
+
+
+def gemm_tile(M, N, K):
+    """gemm_tile of linear.h: wide 0, tall 1, pair 2, small 3, brief 4."""
+    def price(p):
+        bm, bn, per, step, base, step_more, base_more = p
+        full, rest = divmod(-(-M // bm) * -(-N // bn), 256 * per)
+        one = lambda j: (step + step_more * (j - 1)) * (K // 64) + base + base_more * (j - 1)
+        return full * one(per) + (one(-(-rest // 256)) if rest else 0)
+    prices = [price(p) for p in _gemm_prices()]
+    return prices.index(min(prices))
+
+
+# us of a map on the wide, tall, pair, small and brief tiles, measured on an
+# MI355X: short and long reductions, one round of tiles and many, rows and
+# columns that fill the tiles and not.
+GEMM_MEASURED = {
+    (320, 8192, 320): (10.5, 7.5, 7.9, 7.5, 6.5), (640, 2048, 512): (13.5, 9.3, 10.7, 6.8, 7.5),
+    (4096, 768, 320): (10.5, 7.8, 8.1, 7.6, 6.6), (2048, 3072, 256): (11.5, 12.8, 10.9, 11.8, 10.8),
+    (1024, 3072, 768): (16.2, 11.3, 12.8, 12.6, 10.7), (1300, 3072, 768): (17.8, 21.2, 18.6, 15.9, 13.8),
+    (4096, 3072, 768): (31.2, 29.2, 28.3, 37.3, 34.0), (8192, 2304, 768): (47.1, 45.0, 43.1, 54.0, 49.8),
+    (320, 12001, 1024): (26.8, 31.4, 29.5, 22.0, 22.5), (200, 12001, 1024): (25.3, 17.9, 20.1, 18.3, 18.5),
+    (1024, 1024, 4096): (48.6, 32.0, 44.4, 19.9, 30.8), (8192, 1024, 4096): (63.0, 77.3, 70.5, 101.1, 96.0),
+    (1280, 4096, 2048): (29.7, 36.8, 33.6, 35.8, 37.8), (640, 8192, 4096): (58.2, 73.2, 66.0, 78.4, 98.2),
+    (2048, 2048, 2048): (28.9, 21.6, 26.3, 27.6, 26.4), (8192, 8192, 2048): (283.2, 339.5, 309.5, 436.9, 415.9),
+    (1536, 8192, 1024): (35.8, 36.2, 33.6, 45.1, 43.3), (6144, 512, 768): (15.6, 11.1, 12.6, 12.2, 10.3)}
+
+
+@pytest.mark.parametrize("shape", GEMM_MEASURED, ids=str)
+def test_gemm_tile_rule_picks_a_fast_tile(shape):
+    """The tile that the price table gives is within 5% of the fastest one
+    measured (two runs of one tile differ by up to 3%)."""
+    us = GEMM_MEASURED[shape]
+    assert us[gemm_tile(*shape)] <= 1.05 * min(us), (gemm_tile(*shape), us)
+
+
 @pytest.mark.parametrize("BM,BN,NS,WAVES_M,WAVES_N", [(128, 256, 3, 2, 4), (128, 128, 4, 2, 4), (128, 128, 2, 2, 2),
-                                                        (64, 64, 4, 2, 2)])
+                                                        (64, 64, 4, 2, 2), (64, 64, 2, 2, 2)])
 def test_gemm_stage_layout(BM, BN, NS, WAVES_M, WAVES_N):
     """k_gemm's stage in LDS: the DMA instructions of the waves write every
     16-byte slot of it once, from inside the tile's rows, and each operand

@@ -230,14 +230,15 @@ def test_self_attention_argument_errors():
 
 
 # One output row has the same bits whichever kernel computes it: the tiled
-# GEMM at every tile choice (wide, tall, pair, small), at row and column
+# GEMM at every tile choice (wide, tall, pair, small, brief), at row and column
 # remainders of the tiles, and at reductions whose last chunk is short or
 # whose chunks are 512 wide, against the few-row kernel on 64 of its rows.
 @pytest.mark.parametrize("M,N,K,epi", [
     (129, 64, 64, smem.LIN_STORE), (192, 1000, 832, smem.LIN_GELU), (1000, 3072, 768, smem.LIN_STORE),
     (520, 8192, 1088, smem.LIN_GELU), (2047, 2052, 320, smem.LIN_RESID), (8065, 772, 256, smem.LIN_RESID),
     (4100, 4100, 320, smem.LIN_GELU), (8193, 1200, 192, smem.LIN_RESID),
-    (1025, 4100, 4352, smem.LIN_STORE), (257, 516, 8192, smem.LIN_RESID), (136, 9001, 448, smem.LIN_F32)])
+    (1025, 4100, 4352, smem.LIN_STORE), (257, 516, 8192, smem.LIN_RESID), (136, 9001, 448, smem.LIN_F32),
+    (2060, 1800, 1088, smem.LIN_RESID), (4100, 3076, 1088, smem.LIN_GELU)])
 def test_gemm_rows_bitwise_few_row_kernel(M, N, K, epi):
     say("gemm rows", M, N, K, epi)
     g = torch.Generator(device="cuda")
