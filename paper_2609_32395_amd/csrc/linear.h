@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "linear_plan.h"
 
 namespace smem {
 
@@ -54,7 +55,6 @@ __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.f + er
 // operations in the same order for any M and any tiling, which keeps a
 // row's result independent of the other rows in the call (block-skip serving
 // reproduces the cold pass bit for bit).
-__host__ __device__ constexpr int lin_chunk(int K) { return 256 * ((K + 256 * 16 - 1) / (256 * 16)); }
 
 // LayerNorm of a row of width d (d % 64 == 0, d <= 2048), eps 1e-5, with the
 // statistics summed in one fixed order, so the stand-alone kernel below and
@@ -270,18 +270,6 @@ __device__ __forceinline__ f32x4 mfma16(const u32x4& A, const u32x4& B, const f3
                                                  0, 0, 0);
 }
 
-// Launch order -> work item.  Workgroups are dealt to the 8 XCDs round-robin
-// (workgroup i to XCD i mod 8); the grid is padded to a multiple of 8 and
-// item p = (i mod 8) * (T8 / 8) + i / 8, so each XCD takes one contiguous
-// range of items and neighbouring items share that XCD's L2.  Padding
-// workgroups get -1 and exit.
-__device__ __forceinline__ int xcd_order(int i, int T) {
-  const int T8 = (T + 7) & ~7;
-  const int p = (i & 7) * (T8 >> 3) + (i >> 3);
-  return p < T ? p : -1;
-}
-__host__ __device__ constexpr int xcd_grid(int T) { return (T + 7) & ~7; }
-
 // Few rows (one or two blocks, or a batch of decoded tokens): a workgroup
 // owns 16 rows and 16 G columns, and its waves take the reduction chunks side
 // by side, so the loads of the whole tile are in flight at once.  An MFMA
@@ -297,18 +285,6 @@ __host__ __device__ constexpr int xcd_grid(int T) { return (T + 7) & ~7; }
 // -> 7.2, 8192 -> 2048 27.6 -> 16.7; with the LayerNorm 1024 -> 1024 6.6 ->
 // 5.2, 1024 -> 3072 10.5 -> 8.1, 1024 -> 4096 + GELU 10.8 -> 8.2 (2.6 us of it
 // waits for the weights, 0.9 the statistics).
-//
-// LDS: row r of a piece is 32 slots of 16 bytes, chunk q in slot q ^ r, so
-// the 16 rows one operand read touches lie on distinct banks.
-struct FewTile {
-  static constexpr int BYTES = 8192;
-  // write: instruction i of a half-wave holds row r, chunk s = lane % 32
-  __device__ static int put(int r, int s) { return r * 512 + ((s ^ r) << 4); }
-  // operand of step t: lane (row l % 16, group l / 16) reads chunk 4 t + group
-  __device__ static int get(int lane, int t) {
-    return (lane & 15) * 512 + (((t * 4 + (lane >> 4)) ^ (lane & 15)) << 4);
-  }
-};
 
 // The 8 instructions of a 16-row piece: rows row(2 i + lane / 32), chunk
 // lane % 32 of the nt * 4 valid ones from column k (a short last piece
@@ -360,8 +336,9 @@ __device__ __forceinline__ u32x2 few_res(const LinArgs& a, int m0, int n0) {
   }
   return u32x2{0u, 0u};
 }
-// The chunk sums in LDS ([n_chunks][16 RT][16 G]) added in chunk order, stored.
-template <int EPI, int RT, int G>
+// The chunk sums in LDS ([n_chunks][16 RT][16 G]) added in chunk order, stored;
+// res: few_res's word (not AHEAD: loaded here instead).
+template <int EPI, int RT, int G, bool AHEAD = true>
 __device__ __forceinline__ void few_finish(const LinArgs& a, const float* part, int NC, int m0, int n0,
                                            const u32x2& res) {
   for (int q = threadIdx.x; q < 64 * RT * G; q += blockDim.x) {
@@ -376,7 +353,7 @@ __device__ __forceinline__ void few_finish(const LinArgs& a, const float* part, 
         if (c4 + e < NC) v += p[e];
     }
     const int m = m0 + row;
-    if (m < a.M) lin_store4<EPI>(a, m, n0 + c0, v, q < (int)blockDim.x ? &res : nullptr);
+    if (m < a.M) lin_store4<EPI>(a, m, n0 + c0, v, AHEAD && q < (int)blockDim.x ? &res : nullptr);
   }
 }
 // A lane's sums of tile (row tile i, column tile j) of chunk c.
@@ -490,7 +467,9 @@ __global__ void __launch_bounds__(512) k_linear_few_ln(LinArgs a, int row_tiles,
   float* st0 = (float*)(few_lds + NC * WPC * FewTile::BYTES);
   float* st1 = st0 + 128;
   float* part = st1 + 128;
-  const u32x2 res = few_res<EPI, 1, G>(a, m0, n0);
+  constexpr bool AHEAD = GW < 4;                         // four tiles of weights leave no registers for it
+  u32x2 res = {0u, 0u};
+  if constexpr (AHEAD) res = few_res<EPI, 1, G>(a, m0, n0);
   const bool in = s < 4 * nt;
   const int q = in ? s : 0;
   u32x4 X[RI], W[GW][8], g16, b16;
@@ -563,20 +542,8 @@ __global__ void __launch_bounds__(512) k_linear_few_ln(LinArgs a, int row_tiles,
 #pragma unroll
   for (int j = 0; j < GW; ++j) few_part<1, G>(part, c, 0, h * GW + j, acc[j], lane);
   __syncthreads();
-  few_finish<EPI, 1, G>(a, part, NC, m0, n0, res);
+  few_finish<EPI, 1, G, AHEAD>(a, part, NC, m0, n0, res);
 }
-
-// The same for wide rows (K > 1024) and many columns: RT x 16 rows and G x 16
-// columns per workgroup, one wave per chunk, x and W loaded as MFMA fragments
-// (a lane of step t holds piece 4 t + l / 16 of its row, so the statistics'
-// tree is partly between registers), U steps of W in flight.
-// Dynamic LDS: gain and bias (4 K bytes) and two statistics planes of
-// n_chunks x 16 RT floats, then, in the same space, n_chunks x RT x G KiB of
-// partial sums.
-template <int RT_, int G_, int U_>
-struct SkinnyCfg {
-  static constexpr int RT = RT_, G = G_, U = U_;
-};
 
 // An empty asm that claims to rewrite the packed x rows, so the compiler
 // unpacks them again where they are next used instead of keeping 8 floats
@@ -589,9 +556,17 @@ __device__ __forceinline__ void opaque(u32x4 (&X)[T][R]) {
     for (int i = 0; i < R; ++i) asm volatile("" : "+v"(X[t][i]));
 }
 
-template <int EPI, class C>
+// The same for wide rows (K > 1024) and many columns, and for rows of at most
+// 128 values: RT x 16 rows and G x 16 columns per workgroup, one wave per chunk,
+// x and W loaded as MFMA fragments (a lane of step t holds piece 4 t + l / 16 of
+// its row, so the statistics' tree is partly between registers), U steps of W in
+// flight.
+// Dynamic LDS: gain and bias (4 K bytes) and two statistics planes of
+// n_chunks x 16 RT floats, then, in the same space, n_chunks x RT x G KiB of
+// partial sums.
+template <int EPI, int RT, int G, int U>
 __global__ void __launch_bounds__(512) k_linear_skinny_ln(LinArgs a, int row_tiles, int col_groups) {
-  constexpr int RT = C::RT, G = C::G, U = C::U, W16 = 16 * G;
+  constexpr int W16 = 16 * G;
   extern __shared__ float part[];   // [n_chunks][16 RT][16 G]
   const int pid = xcd_order(blockIdx.x, row_tiles * col_groups);
   if (pid < 0) return;
@@ -717,90 +692,48 @@ __global__ void __launch_bounds__(512) k_linear_skinny_ln(LinArgs a, int row_til
   }
 }
 
-inline size_t skinny_ln_lds(int nc, int rt, int g, int K) {
-  return std::max((size_t)nc * 1024 * rt * g, (size_t)4 * K + (size_t)2 * nc * 16 * rt * 4);
+template <int EPI, FewKind KIND>
+static void launch_few_as(const LinArgs& a, hipStream_t s) {
+  constexpr FewPlan p = kFewPlans[KIND];
+  const int rt = ceil_div(a.M, 16 * p.rt), cg = ceil_div(a.N, 16 * p.g);
+  hipLaunchKernelGGL((k_linear_few<EPI, p.rt, p.g, p.nw, p.loop>), dim3(xcd_grid(rt * cg)),
+                     dim3(64 * few_waves(p, a.K)), few_lds_bytes(p, a.K), s, a, rt, cg);
 }
-
-template <int EPI, class C>
-static void launch_skinny_ln_cfg(const LinArgs& a, int nc, hipStream_t s) {
-  const int rt = (a.M + 16 * C::RT - 1) / (16 * C::RT), cg = (a.N + 16 * C::G - 1) / (16 * C::G);
-  hipLaunchKernelGGL((k_linear_skinny_ln<EPI, C>), dim3(xcd_grid(rt * cg)), dim3(64 * nc),
-                     skinny_ln_lds(nc, C::RT, C::G, a.K), s, a, rt, cg);
-}
-
-template <int EPI, int RT, int G, int NW, bool LOOP>
-static void launch_few_cfg(const LinArgs& a, int nc, hipStream_t s) {
-  const int rt = (a.M + 16 * RT - 1) / (16 * RT), cg = (a.N + 16 * G - 1) / (16 * G), nw = std::min(nc, NW);
-  hipLaunchKernelGGL((k_linear_few<EPI, RT, G, NW, LOOP>), dim3(xcd_grid(rt * cg)), dim3(64 * nw),
-                     (size_t)nw * FewTile::BYTES + (size_t)nc * RT * G * 1024, s, a, rt, cg);
-}
-// The tile (row tiles x column tiles of 16, waves) by size; us at 64 rows on
-// 1x1 / 2x1 / 2x2 / 2x4: 1024 -> 1024 3.7 / 4.4 / 5.7 / 8.6, 2048 -> 2048 6.9 /
-// 6.6 / 8.3 / 12.5, 1984 -> 7000 17.6 / 18.6 / 15.9 / 14.2, 2048 -> 50257 102 /
-// 100 / 89 / 85; 128 rows: 2048 -> 2048 10.9 / 10.1 / 8.3 / 12.2, 1024 -> 50257
-// 86 / 72 / 55 / 63.  Up to two 16 x 16 tiles per CU the smallest tile has the
-// most loads in flight; beyond that larger ones read x and W fewer times over,
-// and with K > 1024 and columns for 192 of them the widest.  9 to 16 chunks of
-// 256 (K <= 4096) take 16 waves with a chunk each (4096 -> 1024: 64 rows 7.3
-// on 1x1, 9.1 on 2x1; 128 rows 11.8 and 9.1), longer reductions 8 waves that
-// loop (8192 -> 2048 on 1x1 / 1x2: 32 rows 12.2 / 17.0, 64 rows 20.9 / 16.7).
 template <int EPI>
 static void launch_few(const LinArgs& a, hipStream_t s) {
-  const int nc = (a.K + lin_chunk(a.K) - 1) / lin_chunk(a.K);
-  auto tiles = [&](int rt, int g) {
-    return (long)((a.M + 16 * rt - 1) / (16 * rt)) * ((a.N + 16 * g - 1) / (16 * g));
-  };
-  const long t = tiles(1, 1);
-  if (a.K > 4096) {
-    if (t > 256) launch_few_cfg<EPI, 1, 2, 8, true>(a, nc, s);
-    else launch_few_cfg<EPI, 1, 1, 8, true>(a, nc, s);
-  } else if (nc > 8) {
-    if (t > 256 && a.M > 16) launch_few_cfg<EPI, 2, 1, 16, false>(a, nc, s);
-    else launch_few_cfg<EPI, 1, 1, 16, false>(a, nc, s);
-  } else if (t <= 512 || a.M <= 16) {
-    launch_few_cfg<EPI, 1, 1, 8, false>(a, nc, s);
-  } else if (a.K > 1024 && tiles(2, 4) >= 192) {
-    launch_few_cfg<EPI, 2, 4, 8, false>(a, nc, s);
-  } else if (t >= 1024) {
-    launch_few_cfg<EPI, 2, 2, 8, false>(a, nc, s);
-  } else {
-    launch_few_cfg<EPI, 1, 1, 8, false>(a, nc, s);
+  switch (few_kind(a.M, a.N, a.K)) {
+    case kFew1x1: launch_few_as<EPI, kFew1x1>(a, s); break;
+    case kFew2x2: launch_few_as<EPI, kFew2x2>(a, s); break;
+    case kFew2x4: launch_few_as<EPI, kFew2x4>(a, s); break;
+    case kFewDeep1x1: launch_few_as<EPI, kFewDeep1x1>(a, s); break;
+    case kFewDeep2x1: launch_few_as<EPI, kFewDeep2x1>(a, s); break;
+    case kFewLong1x1: launch_few_as<EPI, kFewLong1x1>(a, s); break;
+    case kFewLong1x2: launch_few_as<EPI, kFewLong1x2>(a, s); break;
   }
 }
 
-template <int EPI, int G, int WPC>
-static void launch_few_ln_cfg(const LinArgs& a, int nc, hipStream_t s) {
-  const int rt = (a.M + 15) / 16, cg = (a.N + 16 * G - 1) / (16 * G);
-  hipLaunchKernelGGL((k_linear_few_ln<EPI, G, WPC>), dim3(xcd_grid(rt * cg)), dim3(64 * nc * WPC),
-                     (size_t)nc * WPC * FewTile::BYTES + 1024 + (size_t)nc * G * 1024, s, a, rt, cg);
+template <int EPI, FewLnKind KIND>
+static void launch_few_ln_as(const LinArgs& a, hipStream_t s) {
+  constexpr FewLnPlan p = kFewLnPlans[KIND];
+  const int rt = ceil_div(a.M, 16 * p.rt), cg = ceil_div(a.N, 16 * p.g);
+  const dim3 grid(xcd_grid(rt * cg)), block(few_ln_threads(p, a.K));
+  if constexpr (p.wpc > 0)
+    hipLaunchKernelGGL((k_linear_few_ln<EPI, p.g, p.wpc>), grid, block, few_ln_lds_bytes(p, a.K), s, a, rt, cg);
+  else
+    hipLaunchKernelGGL((k_linear_skinny_ln<EPI, p.rt, p.g, p.u>), grid, block, few_ln_lds_bytes(p, a.K), s, a, rt, cg);
 }
-// K <= 1024: as many columns per workgroup as leave about one workgroup per
-// CU, since each normalizes its 16 rows anew (us on 1 / 2 / 4 column tiles:
-// 64 rows 1024 -> 1024 5.2 / 5.4 / 7.1, 1024 -> 4096 10.4 / 8.4 / 8.2; 32 rows
-// 1024 -> 4096 7.2 / 6.3 / 8.2; 16 rows 5.7 / 6.2 / 8.3); past 1024 tiles of
-// 16 x 16 two column tiles again (128 rows 1024 -> 3072 13.2 / 10.5 / 13.8).
-// Wider rows with many columns keep 32-row tiles on MFMA-fragment loads
-// (64 rows, 2048 -> 8192: 20.8 against 25.7 us), which normalize half as often.
 template <int EPI>
 static void launch_few_ln(const LinArgs& a, hipStream_t s) {
-  const int nc = (a.K + 255) / 256;
-  const long rt = (a.M + 15) / 16, t = rt * ((a.N + 15) / 16);
-  if (nc <= 4) {
-    if (t <= 256) launch_few_ln_cfg<EPI, 1, 1>(a, nc, s);
-    else if (t <= 512 || t > 1024) launch_few_ln_cfg<EPI, 2, 2>(a, nc, s);
-    else launch_few_ln_cfg<EPI, 4, 2>(a, nc, s);
-    return;
+  switch (few_ln_kind(a.M, a.N, a.K)) {
+    case kLn1x1: launch_few_ln_as<EPI, kLn1x1>(a, s); break;
+    case kLn1x2: launch_few_ln_as<EPI, kLn1x2>(a, s); break;
+    case kLn1x4: launch_few_ln_as<EPI, kLn1x4>(a, s); break;
+    case kLn1x2Two: launch_few_ln_as<EPI, kLn1x2Two>(a, s); break;
+    case kLn1x4Two: launch_few_ln_as<EPI, kLn1x4Two>(a, s); break;
+    case kLnFrag1x1: launch_few_ln_as<EPI, kLnFrag1x1>(a, s); break;
+    case kLnFrag1x2: launch_few_ln_as<EPI, kLnFrag1x2>(a, s); break;
+    case kLnFrag2x4: launch_few_ln_as<EPI, kLnFrag2x4>(a, s); break;
   }
-  if (t <= 512) {
-    launch_few_ln_cfg<EPI, 2, 1>(a, nc, s);
-    return;
-  }
-  auto fits = [&](int r, int g) {
-    const long wgs = (long)((a.M + 16 * r - 1) / (16 * r)) * ((a.N + 16 * g - 1) / (16 * g));
-    return wgs >= 192 && skinny_ln_lds(nc, r, g, a.K) <= 65536;
-  };
-  if (fits(2, 4)) launch_skinny_ln_cfg<EPI, SkinnyCfg<2, 4, 4>>(a, nc, s);
-  else launch_skinny_ln_cfg<EPI, SkinnyCfg<2, 2, 8>>(a, nc, s);
 }
 
 // Many rows: BM x BN tiles, WAVES_M x WAVES_N waves (each (BM/WAVES_M) x
@@ -827,24 +760,6 @@ static void launch_few_ln(const LinArgs& a, hipStream_t s) {
 // cycles, at the 1.92 GHz that this load leaves), 8192 x 8192 x 2048 with GELU
 // 321 -> 299, 8192 x 4096 x 1024 with GELU 90 -> 85, 8192 x 3072 x 1024 64 ->
 // 61, 4096 x 1024 x 1024 18.8 -> 14.6.
-template <int BM_, int BN_, int BK_, int NS_, int WAVES_M, int WAVES_N>
-struct GemmCfg {
-  static constexpr int BM = BM_, BN = BN_, BK = BK_, NS = NS_;
-  static constexpr int NW = WAVES_M * WAVES_N, NT = 64 * NW;
-  static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 16, TN = WN / 16;
-  static constexpr int CPR = BK / 8;                 // 16-byte chunks per LDS row
-  static constexpr int RPI = 1024 / (BK * 2);        // rows per DMA instruction (1 KiB)
-  static constexpr int R256 = 256 / (BK * 2);        // rows per 256 bytes
-  static constexpr int IA = BM / RPI / NW, IB = BN / RPI / NW;
-  static constexpr int STAGE = (BM + BN) * BK;       // elements per stage
-  static constexpr int PER_CU = NS * STAGE * 2 <= 80 * 1024 ? 2 : 1;   // workgroups that fit a CU's LDS
-  static constexpr bool PLAIN = NS == 2;             // no operands fetched ahead of their stage
-  static_assert(!PLAIN || PER_CU == 2, "the next tile's fill needs the pipelined loop's last barrier");
-  static_assert(IA * RPI * NW == BM && IB * RPI * NW == BN, "DMA rows must tile the stage");
-  static_assert(NS >= 2 && NS <= 5, "ring depth");
-  __device__ static constexpr int swz(int r) { return (r / R256) % CPR; }
-};
-
 template <int N>
 __device__ __forceinline__ void wait_stages(int ahead) {
   if (ahead >= 3) wait_vm<3 * N < 63 ? 3 * N : 63>();
@@ -862,19 +777,14 @@ __global__ void __launch_bounds__(C::NT, 2) k_gemm(LinArgs a, int tiles_m, int t
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave % (BM / WM), wn = wave / (BM / WM);
   const int KT = a.K / BK, CT = lin_chunk(a.K) / BK;
-  const int T = tiles_m * tiles_n;
   const uint16_t* ga[IA];
   const uint16_t* gb[IB];
-  // Launch order -> tile: consecutive pids of one XCD, then groups of 8 row
-  // tiles.  A workgroup takes order index i, i + gridDim.x, .. (the grid is a
-  // multiple of 8, so all of them on its XCD).
   int m0 = 0, n0 = 0;
   auto place = [&](int i) {              // false: no tile at order index i
-    const int pid = i < xcd_grid(T) ? xcd_order(i, T) : -1;
-    if (pid < 0) return false;
-    const int per_group = 8 * tiles_n, g0 = (pid / per_group) * 8, gsz = min(tiles_m - g0, 8);
-    m0 = (g0 + (pid % per_group) % gsz) * BM;
-    n0 = ((pid % per_group) / gsz) * BN;
+    const GemmPlace p = gemm_place(i, tiles_m, tiles_n);
+    if (!p.ok) return false;
+    m0 = p.tm * BM;
+    n0 = p.tn * BN;
 #pragma unroll
     for (int i = 0; i < IA; ++i) {
       const int r = (wave * IA + i) * C::RPI + lane / C::CPR, c = (lane % C::CPR) ^ C::swz(r);
@@ -1119,16 +1029,6 @@ __global__ void __launch_bounds__(512) k_linear_wide(LinArgs a, int n_tiles) {
   }
 }
 
-// The wide kernel serves fp32 maps of at most 64 rows with K a multiple of
-// 256 up to 2048 whose x rows fit in LDS (16 row tiles of K + 8 bf16 each:
-// 64 rows up to K = 1024, 32 rows at K = 2048) and at least 8192 columns.
-constexpr int kWideLds = 160 * 1024;
-__host__ __device__ constexpr int wide_lds(int rt, int k) { return rt * 16 * (k + 8) * 2; }
-inline bool wide_fits(const LinArgs& a) {
-  return !a.lng && a.M >= 1 && a.M <= 64 && a.K % 256 == 0 && a.K <= 2048 && a.N >= 8192 && a.ldx % 8 == 0 &&
-         wide_lds((a.M + 15) / 16, a.K) <= kWideLds;
-}
-
 template <int NCH, int RT>
 static void launch_wide_rt(const LinArgs& a, int n_tiles, dim3 grid, hipStream_t s) {
   if constexpr (wide_lds(RT, 256 * NCH) <= kWideLds)
@@ -1163,59 +1063,7 @@ static void launch_wide(const LinArgs& a, hipStream_t s) {
 template <int EPI, class C>
 static void launch_gemm(const LinArgs& a, hipStream_t s) {
   const int tm = (a.M + C::BM - 1) / C::BM, tn = (a.N + C::BN - 1) / C::BN;
-  const int grid = C::PER_CU == 1 ? std::min(xcd_grid(tm * tn), 256) : xcd_grid(tm * tn);
-  hipLaunchKernelGGL((k_gemm<EPI, C>), dim3(grid), dim3(C::NT), 0, s, a, tm, tn);
-}
-
-// The tiles of a many-row map.  A wide tile moves fewer bytes from L2 into
-// LDS per product (the DMA, not the LDS reads, is what the main loop waits
-// for: with it taken out the 128 x 256 loop runs at 1420 instead of 1080
-// TFLOP/s), a small one fills the 256 CUs on small outputs.
-using GemmWide = GemmCfg<128, 256, 64, 3, 2, 4>;   // one workgroup of 8 waves per CU (144 KB of LDS)
-using GemmTall = GemmCfg<128, 128, 64, 4, 2, 4>;   // one of 8 waves per CU (128 KB)
-using GemmPair = GemmCfg<128, 128, 64, 2, 2, 2>;   // two of 4 waves per CU (64 KB each)
-using GemmSmall = GemmCfg<64, 64, 64, 4, 2, 2>;    // two of 4 waves per CU (64 KB each)
-using GemmBrief = GemmCfg<64, 64, 64, 2, 2, 2>;    // four of 4 waves per CU (32 KB each): short reductions
-enum GemmTile { kGemmWide, kGemmTall, kGemmPair, kGemmSmall, kGemmBrief };
-
-// The tile of an M x N x K map: the cheapest by rounds over the 256 CUs.  A
-// round of a tile is priced by what its workgroups take when j of them share a
-// CU, (step + step_more (j - 1)) per 64 columns of K plus base + base_more (j -
-// 1) for their start and end, in hundredths of a us: over 1994 measured maps (M
-// 129 .. 8192, N 64 .. 12001, K 64 .. 8192, every epilogue) the choice costs
-// 0.3% over the best tile on average, and more than 5% in one of a hundred.  A
-// wide tile moves the fewest bytes per product but starts slowest, so the price
-// has to know K.  us on wide / tall / pair / small / brief tiles: 320 x 8192 x
-// 320 10.5 / 7.5 / 7.9 / 7.5 / 6.5, 640 x 2048 x 512 13.5 / 9.3 / 10.7 / 6.8 /
-// 7.5, 2048 x 3072 x 256 11.5 / 12.8 / 10.9 / 11.8 / 10.8, 1024 x 3072 x 768
-// 16.2 / 11.3 / 12.8 / 12.6 / 10.7, 8192 x 2304 x 768 47.1 / 45.0 / 43.1 / 54.0
-// / 49.8, 640 x 8192 x 4096 58 / 73 / 66 / 78 / 98, 8192 x 8192 x 2048 283 /
-// 340 / 310 / 437 / 416.
-struct GemmPrice {
-  int bm, bn, per_cu, step, base, step_more, base_more;
-};
-constexpr GemmPrice kGemmPrice[] = {
-    {128, 256, 1, 76, 625, 0, 0},    // wide
-    {128, 128, 1, 47, 350, 0, 0},    // tall
-    {128, 128, 2, 62, 298, 30, 223}, // pair
-    {64, 64, 2, 22, 107, 14, 56},    // small
-    {64, 64, 4, 32, 68, 13, 61},     // brief
-};
-inline GemmTile gemm_tile(int M, int N, int K) {
-  int best = 0;
-  long least = 0;
-  for (int i = 0; i < 5; ++i) {
-    const GemmPrice& p = kGemmPrice[i];
-    const long tiles = (long)((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn);
-    auto round = [&](long j) { return (p.step + p.step_more * (j - 1)) * (K / 64) + p.base + p.base_more * (j - 1); };
-    const long full = tiles / (256 * p.per_cu), rest = tiles % (256 * p.per_cu);
-    const long price = full * round(p.per_cu) + (rest ? round((rest + 255) / 256) : 0);
-    if (i == 0 || price < least) {
-      least = price;
-      best = i;
-    }
-  }
-  return (GemmTile)best;
+  hipLaunchKernelGGL((k_gemm<EPI, C>), dim3(gemm_grid(C::PER_CU, tm * tn)), dim3(C::NT), 0, s, a, tm, tn);
 }
 
 template <int EPI>
@@ -1237,7 +1085,7 @@ static hipError_t linear(const LinArgs& a, hipStream_t s) {
     n.lng = n.lnb = nullptr;
     return linear<EPI>(n, s);
   }
-  if (EPI == kLinF32 && wide_fits(a)) {
+  if (EPI == kLinF32 && a.ldx % 8 == 0 && wide_fits(a.M, a.N, a.K)) {
     launch_wide(a, s);
   } else if (a.M <= 128) {
     launch_few<EPI>(a, s);

@@ -5,9 +5,12 @@ this mirrors the largest element offset each kernel touches in each buffer
 (from its loop bounds and lane mappings) and checks it lies inside the buffer
 the ABI sizes for it.  It runs before any kernel change goes to a GPU: an
 access past a tensor's end is caught here, not as a memory fault."""
+import ctypes
+import functools
 import itertools
 import os
-import re
+import subprocess
+import tempfile
 
 import pytest
 
@@ -410,26 +413,93 @@ def test_model_kernel_indexing(d, vocab, rows):
     assert 3 * 512 + 63 * 8 + 8 >= 2048         # the four chunks cover d = 2048
 
 
-def _source(name):
-    return open(os.path.join(os.path.dirname(__file__), "..", "paper_2609_32395_amd", "csrc", name)).read()
+@functools.lru_cache(None)
+def plan():
+    """The library's own linear-map plan, compiled from its header."""
+    here = os.path.dirname(os.path.abspath(__file__))
+    out = os.path.join(tempfile.mkdtemp(), "linear_plan.so")
+    csrc = os.path.join(here, "..", "paper_2609_32395_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", csrc,
+                    os.path.join(here, "native", "linear_plan_c.cpp"), "-o", out], check=True)
+    return ctypes.CDLL(out)
 
 
-def _gemm_prices():
-    """kGemmPrice of linear.h: rows per tile, columns per tile, workgroups per
-    CU, step, base, step_more, base_more."""
-    body = re.search(r"kGemmPrice\[\] = \{(.*?)\};", _source("linear.h"), re.S).group(1)
-    return [tuple(int(x) for x in m.split(",")) for m in re.findall(r"\{([-0-9, ]+)\}", body)]
+def _ints(fn, n, *args):
+    o = (ctypes.c_int * n)()
+    fn(*args, o)
+    return list(o)
 
 
 def gemm_tile(M, N, K):
-    """gemm_tile of linear.h: wide 0, tall 1, pair 2, small 3, brief 4."""
-    def price(p):
-        bm, bn, per, step, base, step_more, base_more = p
-        full, rest = divmod(-(-M // bm) * -(-N // bn), 256 * per)
-        one = lambda j: (step + step_more * (j - 1)) * (K // 64) + base + base_more * (j - 1)
-        return full * one(per) + (one(-(-rest // 256)) if rest else 0)
-    prices = [price(p) for p in _gemm_prices()]
-    return prices.index(min(prices))
+    """wide 0, tall 1, pair 2, small 3, brief 4"""
+    return plan().lp_gemm_tile(M, N, K)
+
+
+def test_few_row_launches_fit():
+    """Every few-row launch, whatever its size: LDS within a CU's 160 KB,
+    threads within the kernels' launch bounds, and a wave per chunk unless the
+    waves loop."""
+    kinds, ln_kinds = set(), set()
+    for M, N, K in itertools.product((1, 16, 17, 48, 64, 100, 128), (4, 64, 516, 1024, 3072, 4096, 8200, 20000, 50257),
+                                     list(range(64, 2049, 64)) + [2112, 3008, 4096, 4160, 6144, 8192, 16384]):
+        k = plan().lp_few_kind(M, N, K)
+        RT, G, nw, loop, lds = _ints(plan().lp_few_plan, 5, k, K)
+        NC = -(-K // lin_chunk(K))
+        assert lds == nw * 8192 + NC * RT * G * 1024 <= 160 * 1024 and (loop or nw == NC)
+        assert loop or lin_chunk(K) == 256        # one piece of 8 steps holds a whole chunk
+        assert nw <= (16 if k in (3, 4) else 8)   # the kernels' launch bounds
+        kinds.add(k)
+        if K > 2048:
+            continue
+        k = plan().lp_few_ln_kind(M, N, K)
+        RT, G, wpc, u, threads, lds = _ints(plan().lp_few_ln_plan, 6, k, K)
+        assert threads == 64 * NC * max(1, wpc) <= 512 and lds <= 160 * 1024 and lin_chunk(K) == 256 and NC <= 8
+        assert wpc in (0, 1, 2) and (wpc == 0 or (RT == 1 and G % wpc == 0))
+        ln_kinds.add(k)
+    assert kinds == set(range(7)) and ln_kinds == set(range(8))   # every tile is reached
+
+
+# us of a map, measured on an MI355X with the weights out of the caches.
+# Without LayerNorm (K <= 2048) on 1x1, 2x2 and 2x4 tiles:
+FEW_MEASURED = {
+    (64, 1024, 1024): (4.1, 6.0, 8.8), (64, 2048, 2048): (6.7, 7.8, 11.4), (64, 50256, 2048): (98.7, 86.0, 79.8),
+    (32, 8192, 64): (3.6, 4.7, 6.8), (32, 8192, 256): (4.4, 5.6, 7.6), (128, 2048, 256): (3.7, 4.8, 7.1),
+    (128, 8192, 512): (9.5, 8.2, 9.3), (128, 50256, 1024): (84.1, 50.2, 58.1), (48, 12000, 1088): (14.6, 17.2, 19.7),
+    (16, 12000, 1984): (13.5, 17.4, 15.8), (64, 3072, 1536): (7.7, 7.3, 10.2), (128, 8192, 320): (9.4, 7.8, 9.0),
+    (128, 4096, 1088): (11.9, 11.2, 10.1), (96, 3072, 1088): (8.4, 10.9, 9.7), (96, 6144, 2048): (20.8, 21.0, 23.2)}
+# with it, by kind:
+FEW_LN_MEASURED = {
+    (64, 512, 64): {0: 4.7, 1: 5.4, 2: 6.8, 3: 4.4, 4: 5.2, 5: 4.0, 6: 4.2, 7: 7.2},
+    (128, 4096, 64): {0: 6.9, 1: 6.5, 2: 7.5, 3: 5.8, 4: 6.7, 5: 7.2, 6: 5.4, 7: 7.3},
+    (64, 3072, 256): {0: 5.1, 1: 5.6, 2: 6.7, 3: 4.9, 4: 5.1, 5: 5.4, 6: 5.4, 7: 8.7},
+    (32, 4096, 512): {0: 6.3, 1: 6.0, 2: 7.2, 3: 5.0, 4: 5.8, 5: 7.1, 6: 5.8, 7: 9.3},
+    (128, 8192, 512): {0: 17.1, 1: 14.5, 2: 11.2, 3: 12.0, 4: 10.8, 5: 20.9, 6: 17.2, 7: 12.8},
+    (64, 1024, 1024): {0: 5.6, 1: 6.3, 2: 7.9, 3: 5.7, 4: 7.3, 5: 6.5, 6: 7.3, 7: 11.6},
+    (64, 2048, 768): {0: 6.7, 1: 6.2, 2: 7.9, 3: 5.6, 4: 7.0, 5: 7.9, 6: 6.4, 7: 10.6},
+    (64, 4096, 1024): {0: 10.2, 1: 8.5, 2: 8.3, 3: 8.1, 4: 7.7, 5: 12.6, 6: 10.2, 7: 11.6},
+    (128, 3072, 768): {0: 11.8, 1: 10.6, 2: 10.7, 3: 9.9, 4: 11.7, 5: 14.3, 6: 11.3, 7: 10.6},
+    (128, 4096, 1024): {0: 16.4, 1: 13.4, 2: 11.0, 3: 12.6, 4: 13.0, 5: 20.7, 6: 15.4, 7: 11.8},
+    (1, 50256, 768): {0: 22.7, 1: 21.3, 2: 21.6, 3: 22.2, 4: 25.5, 5: 23.8, 6: 19.4, 7: 24.3},
+    (16, 2048, 2048): {0: 7.1, 1: 8.7, 2: 11.7, 5: 9.4, 6: 10.9, 7: 16.2},
+    (64, 2048, 1088): {0: 11.3, 1: 8.5, 2: 10.4, 5: 13.3, 6: 8.9, 7: 13.8},
+    (16, 12000, 1536): {0: 17.4, 1: 17.6, 2: 14.2, 5: 24.1, 6: 19.4, 7: 17.6},
+    (64, 3072, 2048): {0: 17.0, 1: 15.8, 2: 11.8, 5: 23.4, 6: 19.5, 7: 17.5},
+    (64, 8192, 2048): {0: 40.9, 1: 33.2, 2: 25.2, 5: 59.1, 6: 37.7, 7: 21.0},
+    (17, 12000, 1088): {0: 28.2, 1: 22.1, 2: 20.3, 5: 35.1, 6: 22.7, 7: 15.0}}
+
+
+@pytest.mark.parametrize("shape", FEW_MEASURED, ids=str)
+def test_few_row_rule_picks_a_fast_tile(shape):
+    us = FEW_MEASURED[shape]
+    kind = plan().lp_few_kind(*shape)
+    assert us[kind] <= 1.1 * min(us), (kind, us)
+
+
+@pytest.mark.parametrize("shape", FEW_LN_MEASURED, ids=str)
+def test_few_row_layernorm_rule_picks_a_fast_tile(shape):
+    us = FEW_LN_MEASURED[shape]
+    kind = plan().lp_few_ln_kind(*shape)
+    assert us[kind] <= 1.1 * min(us.values()), (kind, us)
 
 
 # us of a map on the wide, tall, pair, small and brief tiles, measured on an

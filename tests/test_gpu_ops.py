@@ -262,7 +262,9 @@ def test_gemm_rows_bitwise_few_row_kernel(M, N, K, epi):
     (17, 2048, 1088, True, smem.LIN_STORE), (70, 6148, 1984, True, smem.LIN_STORE), (128, 5000, 2048, True, smem.LIN_F32),
     (1, 4, 64, False, smem.LIN_STORE), (63, 1028, 1024, False, smem.LIN_RESID), (128, 2052, 2048, False, smem.LIN_RESID),
     (49, 7001, 1984, False, smem.LIN_F32), (100, 4100, 448, False, smem.LIN_GELU), (31, 1024, 4096, False, smem.LIN_RESID),
-    (113, 772, 2368, False, smem.LIN_RESID), (64, 2048, 8192, False, smem.LIN_RESID), (9, 516, 4672, False, smem.LIN_STORE)])
+    (113, 772, 2368, False, smem.LIN_RESID), (64, 2048, 8192, False, smem.LIN_RESID), (9, 516, 4672, False, smem.LIN_STORE),
+    (100, 2052, 128, True, smem.LIN_GELU), (128, 3500, 1024, True, smem.LIN_RESID), (12, 25000, 768, True, smem.LIN_STORE),
+    (7, 20004, 2048, True, smem.LIN_STORE), (90, 6000, 512, True, smem.LIN_RESID), (40, 9000, 1088, False, smem.LIN_STORE)])
 def test_few_rows_bitwise_many_rows(M, N, K, ln, epi):
     say("few rows", M, N, K, ln, epi)
     g = torch.Generator(device="cuda")
