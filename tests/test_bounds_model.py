@@ -25,22 +25,11 @@ def pages_per_split(n_read, min_pages, cap=SPLIT_CAP):
     return max(min_pages, -(-n_read // cap))
 
 
-def xcd_grid(T):
-    return (T + 7) // 8 * 8
-
-
-def xcd_order(i, T):
-    """Launch order -> work item of the linear-map kernels: workgroup i runs on
-    XCD i % 8; each XCD takes a contiguous range of items; padding gets -1."""
-    p = (i & 7) * (xcd_grid(T) >> 3) + (i >> 3)
-    return p if p < T else -1
-
-
 def test_xcd_order_is_a_bijection():
     for T in list(range(1, 70)) + [384, 3142, 50257]:
-        items = [xcd_order(i, T) for i in range(xcd_grid(T))]
+        items = [plan().lp_xcd_order(i, T) for i in range(plan().lp_xcd_grid(T))]
         assert sorted(p for p in items if p >= 0) == list(range(T))
-        per = xcd_grid(T) // 8          # each XCD's items are one contiguous range
+        per = plan().lp_xcd_grid(T) // 8    # each XCD's items are one contiguous range
         for x in range(8):
             mine = [p for i, p in enumerate(items) if i % 8 == x and p >= 0]
             assert mine == list(range(x * per, min(T, (x + 1) * per)))
@@ -262,157 +251,6 @@ def test_rows_reader_indexing(b, D):
     assert 32 <= 64
 
 
-def lin_chunk(K):
-    return 256 * ((K + 256 * 16 - 1) // (256 * 16))
-
-
-def _linear_ranges(M, N, K, ldx, ldy, n2, ns, split):
-    """Largest element index each linear-map kernel touches, from the
-    kernels' own index arithmetic, for the kernel the host picks:
-    k_linear_skinny (M <= 128), k_gemm<128,128> or k_gemm<64,64>."""
-    hi = {"x": -1, "w": -1, "w2": -1, "y": -1, "lds": -1}
-
-    def wrow(n, k_last):
-        key, row = ("w", n) if n < n2 else ("w2", n - n2)
-        hi[key] = max(hi[key], row * K + k_last)
-
-    def out(m, n):
-        if m < M and n < N:
-            if split:
-                g, c = divmod(n, ns)
-                assert g < 3 and c < ns
-                hi["y"] = max(hi["y"], m * ns + c)
-            else:
-                hi["y"] = max(hi["y"], m * ldy + n)
-
-    def out4(m, n):                           # lin_store4: columns n .. n+3 of row m, n % 4 == 0
-        assert n % 4 == 0 and (ldy % 4 == 0 or not split)
-        for e in range(4):
-            out(m, n + e)
-
-    lanes = (0, 15, 16, 47, 48, 63)
-    if M <= 128:
-        KS, CS = K // 32, lin_chunk(K) // 32
-        NC = -(-KS // CS)
-        fits = lambda rt, g: (-(-M // (16 * rt)) * -(-N // (16 * g)) >= 192 and NC * rt * g <= 64
-                              and (rt == 1 or M > 16))
-        RT, G = next(c for c in ((2, 4), (2, 2), (1, 2), (1, 1)) if c == (1, 1) or fits(*c))   # launch_skinny
-        PART = 256 * RT * G                      # floats per chunk
-        assert NC <= 16 and NC * PART * 4 <= 64 * 1024
-        rt, cg = -(-M // (16 * RT)), -(-N // (16 * G))
-        T = rt * cg
-        tiles = set()
-        for p in range(xcd_grid(T)):
-            pid = xcd_order(p, T)
-            if pid >= 0:
-                tiles.add((pid % rt, pid // rt))
-        assert tiles == set(itertools.product(range(rt), range(cg)))
-        for r_t, g in tiles:
-            m0, n0 = r_t * 16 * RT, g * 16 * G
-            for lane in lanes:
-                kofs = (lane >> 4) * 8
-                last = (KS - 1) * 32 + kofs + 7             # st = min(u0 + u, s1 - 1) * 32 <= (KS - 1) * 32
-                for i in range(RT):
-                    hi["x"] = max(hi["x"], min(m0 + i * 16 + (lane & 15), M - 1) * ldx + last)
-                for j in range(G):
-                    wrow(min(n0 + j * 16 + (lane & 15), N - 1), last)
-                for i, j in itertools.product(range(RT), range(G)):
-                    hi["lds"] = max(hi["lds"], (NC - 1) * PART + (i * 16 + (lane & 15)) * 16 * G + j * 16
-                                    + 4 * (lane >> 4) + 3)
-            for q in range(64 * RT * G):
-                row, c0 = q // (4 * G), (q % (4 * G)) * 4
-                hi["lds"] = max(hi["lds"], (NC - 1) * PART + row * 16 * G + c0 + 3)
-                if m0 + row < M:
-                    out4(m0 + row, n0 + c0)
-        assert hi["lds"] < NC * PART
-        return hi
-    big = -(-N // 128) * -(-M // 128) >= 256
-    BM = BN = 128 if big else 64
-    BK, WAVES_M, WAVES_N = 64, 2, 2                # GemmCfg of every tile size
-    NS = 4 if not big and K >= 3072 else 2         # mid tiles over a long reduction keep four stages
-    NW = WAVES_M * WAVES_N
-    WM, WN = BM // WAVES_M, BN // WAVES_N
-    CPR, RPI, R256 = BK // 8, 1024 // (BK * 2), 256 // (BK * 2)
-    IA, IB = BM // RPI // NW, BN // RPI // NW
-    STAGE = (BM + BN) * BK
-    KT = K // BK
-    swz = lambda r: (r // R256) % CPR
-    tm_, tn_ = -(-M // BM), -(-N // BN)
-    T = tm_ * tn_
-    seen = set()
-    for p in range(xcd_grid(T)):                   # launch order -> tile: a bijection onto the tiles
-        pid = xcd_order(p, T)
-        if pid < 0:
-            continue
-        per_group = 8 * tn_
-        g0 = (pid // per_group) * 8
-        gsz = min(tm_ - g0, 8)
-        seen.add((g0 + (pid % per_group) % gsz, (pid % per_group) // gsz))
-    assert seen == set(itertools.product(range(tm_), range(tn_)))
-    for by, bx in sorted(seen)[:: max(1, len(seen) // 40)] + [(tm_ - 1, tn_ - 1)]:
-        n0, m0 = bx * BN, by * BM
-        for wave, lane in itertools.product(range(NW), range(64)):
-            for i in range(IA):                  # A: DMA source and LDS destination of instruction i
-                r = (wave * IA + i) * RPI + lane // CPR
-                c = (lane % CPR) ^ swz(r)
-                hi["x"] = max(hi["x"], min(m0 + r, M - 1) * ldx + c * 8 + (KT - 1) * BK + 7)
-                dst = (NS - 1) * STAGE * 2 + (wave * IA + i) * 1024 + 16 * lane + 15
-                assert r < BM and dst - (NS - 1) * STAGE * 2 < BM * BK * 2
-            for i in range(IB):
-                r = (wave * IB + i) * RPI + lane // CPR
-                c = (lane % CPR) ^ swz(r)
-                wrow(min(n0 + r, N - 1), c * 8 + (KT - 1) * BK + 7)
-                dst = (NS - 1) * STAGE * 2 + BM * BK * 2 + (wave * IB + i) * 1024 + 16 * lane + 15
-                assert r < BN and dst < NS * STAGE * 2
-        for wave, lane in itertools.product(range(NW), lanes):
-            wm, wn = wave % WAVES_M, wave // WAVES_M
-            for ks in range(BK // 32):
-                c = ks * 4 + (lane >> 4)
-                for i in range(WM // 16):        # operand reads: row r, slot c ^ swz(r), 8 elements
-                    r = wm * WM + i * 16 + (lane & 15)
-                    assert r < BM and r * BK + ((c ^ swz(r)) << 3) + 7 < BM * BK
-                for j in range(WN // 16):
-                    r = wn * WN + j * 16 + (lane & 15)
-                    assert r < BN and BM * BK + r * BK + ((c ^ swz(r)) << 3) + 7 < STAGE
-            for i, j in itertools.product(range(WM // 16), range(WN // 16)):
-                m = m0 + wm * WM + i * 16 + (lane & 15)
-                if m < M:
-                    out4(m, n0 + wn * WN + j * 16 + 4 * (lane >> 4))
-    return hi
-
-
-@pytest.mark.parametrize("d,vocab,rows", [(128, 256, 448), (768, 1000, 130), (2048, 77, 64), (256, 300, 100),
-                                         (768, 50257, 64), (1024, 4000, 4096), (832, 300, 256), (2048, 300, 256),
-                                         (2048, 50257, 520), (2048, 50257, 136), (2048, 50257, 1), (832, 1000, 200)])
-def test_model_kernel_indexing(d, vocab, rows):
-    """Every linear-map launch the model makes stays inside its operands (x
-    [rows, K] in a [max_tokens, ldx] buffer, W [N or n2, K] and [N - n2, K],
-    y [rows, ldy]); LayerNorm and embedding lanes stay inside a d-wide row."""
-    calls = [  # M, N, K, ldx, ldy, n2, ns, split, rows of W (first, second)
-        (rows, 3 * d, d, d, d, 3 * d, d, True, 3 * d, 0),        # qkv, split into q, k, v
-        (rows, d, d, d, d, d, 0, False, d, 0),                   # attention out (+ residual)
-        (rows, 4 * d, d, d, 4 * d, 4 * d, 0, False, 4 * d, 0),   # ffn up
-        (rows, d, 4 * d, 4 * d, d, d, 0, False, d, 0),           # ffn down (+ residual)
-        (rows, 2 * d, d, d, d, d, d, True, d, d),                # memory K | V maps
-        (1, 2 * d, d, d, 2 * d, d, 0, False, d, d),              # null row through K | V
-        (rows, vocab, d, d, vocab, vocab, 0, False, vocab, 0),   # output head (fp32)
-    ]
-    for M, N, K, ldx, ldy, n2, ns, split, wrows, w2rows in calls:
-        assert K % 64 == 0 and K <= ldx
-        hi = _linear_ranges(M, N, K, ldx, ldy, n2, ns, split)
-        assert hi["x"] < M * ldx
-        assert hi["w"] < wrows * K
-        assert hi["w2"] < max(w2rows, 0) * K or hi["w2"] == -1
-        assert hi["y"] < (M * ns if split else M * ldy)
-    # embedding: lane chunks c = i*512 + 8*lane (i < 4) guarded by c < d, 8 values each
-    assert d % 8 == 0 and d <= 2048
-    for i, lane in itertools.product(range(4), range(64)):
-        c = i * 512 + lane * 8
-        if c < d:
-            assert c + 7 < d
-    assert 3 * 512 + 63 * 8 + 8 >= 2048         # the four chunks cover d = 2048
-
-
 @functools.lru_cache(None)
 def plan():
     """The library's own linear-map plan, compiled from its header."""
@@ -433,6 +271,226 @@ def _ints(fn, n, *args):
 def gemm_tile(M, N, K):
     """wide 0, tall 1, pair 2, small 3, brief 4"""
     return plan().lp_gemm_tile(M, N, K)
+
+
+def lin_chunk(K):
+    return 256 * ((K + 256 * 16 - 1) // (256 * 16))
+
+
+def _some(n):
+    """First, last and a few indices between of n."""
+    return sorted({0, 1, n // 3, n // 2, n - 2, n - 1} & set(range(n)))
+
+
+def _walk(T, rt):
+    """(row tile, column group) of every launch index of a few-row map: each pair once."""
+    seen = [plan().lp_xcd_order(i, T) for i in range(plan().lp_xcd_grid(T))]
+    seen = [(p % rt, p // rt) for p in seen if p >= 0]
+    assert len(seen) == len(set(seen)) == T
+    return seen
+
+
+class _Map:
+    """Largest element index that a linear map's kernel touches in each operand."""
+
+    def __init__(self, M, N, K, ldx, ldy, n2, ns, split):
+        self.__dict__.update(M=M, N=N, K=K, ldx=ldx, ldy=ldy, n2=n2, ns=ns, split=split)
+        self.hi = {"x": -1, "w": -1, "w2": -1, "y": -1}
+        self.done = set()                     # (row, column) of the outputs stored, where asked for
+
+    def x(self, m, k):
+        assert 0 <= m < self.M and 0 <= k and k + 7 < self.K
+        self.hi["x"] = max(self.hi["x"], m * self.ldx + k + 7)
+
+    def w(self, n, k):
+        assert 0 <= n < self.N and 0 <= k and k + 7 < self.K
+        key, row = ("w", n) if n < self.n2 else ("w2", n - self.n2)
+        self.hi[key] = max(self.hi[key], row * self.K + k + 7)
+
+    def out4(self, m, n):                     # lin_store4: columns n .. n + 3 of row m
+        assert n % 4 == 0 and (self.ldy % 4 == 0 or not self.split)
+        for e in range(4):
+            if m < self.M and n + e < self.N:
+                self.done.add((m, n + e))
+                if self.split:
+                    g, c = divmod(n + e, self.ns)
+                    assert g < 3 and c < self.ns
+                    self.hi["y"] = max(self.hi["y"], m * self.ns + c)
+                else:
+                    self.hi["y"] = max(self.hi["y"], m * self.ldy + n + e)
+
+
+def _few_load(row, k, nt, load):
+    """few_load: 8 instructions of two 512-byte rows; the chunks that a short
+    last piece does not have are re-reads of its first."""
+    for i, lane in itertools.product(range(8), (0, 1, 31, 32, 63)):
+        s = lane & 31
+        load(row(2 * i + (lane >> 5)), k + (s if s < 4 * nt else 0) * 8)
+
+
+def _few_finish(o, RT, G, threads, NC, m0, n0, part, lds):
+    for q in range(64 * RT * G):              # few_finish, all strides of the workgroup
+        row, c0 = q // (4 * G), (q % (4 * G)) * 4
+        assert part + (((NC - 1) * 16 * RT + row) * 16 * G + c0) * 4 + 16 <= lds
+        if m0 + row < o.M:
+            o.out4(m0 + row, n0 + c0)
+
+
+def _few_range(o):
+    """k_linear_few."""
+    M, N, K = o.M, o.N, o.K
+    RT, G, nw, loop, lds = _ints(plan().lp_few_plan, 5, plan().lp_few_kind(M, N, K), K)
+    KS, CS = K // 32, lin_chunk(K) // 32
+    NC = -(-KS // CS)
+    assert 1 <= nw <= 16 and lds <= 160 * 1024 and (loop or NC <= nw)
+    part = nw * 8192
+    assert part + NC * RT * G * 1024 <= lds
+    # every wave's pieces: chunks w, w + nw, .. in ascending steps, at most 8 at a time
+    pieces = []
+    for w in range(nw):
+        c, st = w, w * CS
+        while c < NC:
+            nt = min(8, min(KS, (c + 1) * CS) - st)
+            assert nt >= 1 and (loop or st == c * CS)
+            pieces.append((w, c, st, nt))
+            st += 8
+            if st >= min(KS, (c + 1) * CS):
+                if not loop:
+                    break
+                c += nw
+                st = c * CS
+    steps = sorted(s for _, _, st, nt in pieces for s in range(st, st + nt))
+    assert steps == list(range(KS))           # each step of K once
+    assert all(s // CS == c for _, c, st, nt in pieces for s in range(st, st + nt))
+    rt, cg = -(-M // (16 * RT)), -(-N // (16 * G))
+    tiles = _walk(rt * cg, rt)
+    for r_t, g in {tiles[i] for i in _some(len(tiles))} | {(rt - 1, cg - 1), (0, cg - 1), (rt - 1, 0)}:
+        m0, n0 = r_t * 16 * RT, g * 16 * G
+        for w, c, st, nt in pieces:
+            for i in range(RT):
+                _few_load(lambda r: min(m0 + i * 16 + r, M - 1), st * 32, nt, o.x)
+            for j in range(G):
+                _few_load(lambda r: min(n0 + j * 16 + r, N - 1), st * 32, nt, o.w)
+            for i, j, lane in itertools.product(range(RT), range(G), (0, 15, 16, 63)):
+                at = part + (((c * RT + i) * 16 + (lane & 15)) * 16 * G + j * 16 + 4 * (lane >> 4)) * 4
+                assert at % 16 == 0 and at + 16 <= lds
+        _few_finish(o, RT, G, 64 * nw, NC, m0, n0, part, lds)
+        assert all((m, n) in o.done for m in range(m0, min(m0 + 16 * RT, M)) for n in range(n0, min(n0 + 16 * G, N)))
+
+
+def _wide_range(o):
+    """k_linear_wide: x rows once into LDS, two column tiles per wave."""
+    M, N, K = o.M, o.N, o.K
+    RT, XP, n_tiles = -(-M // 16), K + 8, -(-N // 16)
+    assert plan().lp_wide_lds(RT, K) == RT * 16 * XP * 2 <= 160 * 1024
+    for q in range(RT * 16 * (K // 8)):
+        r, c8 = q // (K // 8), q % (K // 8)
+        assert r * XP + c8 * 8 + 8 <= RT * 16 * XP
+        if r < M:
+            o.x(r, c8 * 8)
+    tiles = set()
+    for blk, wave in itertools.product(range(-(-n_tiles // 16)), range(8)):
+        t0 = (blk * 8 + wave) * 2
+        if t0 >= n_tiles:
+            continue
+        for t in {t0, t0 + 1 if t0 + 1 < n_tiles else t0}:
+            tiles.add(t)
+            if t in (0, n_tiles - 1):
+                for lane in (0, 15, 16, 63):
+                    n = min(t * 16 + (lane & 15), N - 1)
+                    for c, u in itertools.product((0, K // 256 - 1), (0, 7)):
+                        o.w(n, (lane >> 4) * 8 + c * 256 + u * 32)
+                    for i in range(RT):
+                        if i * 16 + (lane & 15) < M:
+                            o.out4(i * 16 + (lane & 15), t * 16 + 4 * (lane >> 4))
+    assert tiles == set(range(n_tiles))
+
+
+def _gemm_range(o):
+    """k_gemm on the tile the host picks."""
+    M, N, K = o.M, o.N, o.K
+    tile = gemm_tile(M, N, K)
+    BM, BN, BK, NS, NW, WM, WN, IA, IB, RPI, CPR, STAGE, PER = _ints(plan().lp_gemm_cfg, 13, tile)
+    assert NS * STAGE * 2 <= 160 * 1024 // PER and K % BK == 0
+    tm_, tn_ = -(-M // BM), -(-N // BN)
+    T = tm_ * tn_
+    grid = plan().lp_gemm_grid(PER, T)
+    seen = []
+    for wg in range(grid):                    # a workgroup that fills its CU takes tile after tile
+        i = wg
+        while True:
+            p = plan().lp_gemm_place(i, tm_, tn_)
+            if p < 0:
+                break
+            seen.append(p)
+            if PER != 1:
+                break
+            i += grid
+    assert sorted(seen) == list(range(T))     # every tile once
+    assert grid % 8 == 0                      # so a workgroup's tiles are its XCD's
+    for p in {seen[i] for i in _some(T)} | {T - 1, tn_ - 1}:
+        m0, n0 = p // tn_ * BM, p % tn_ * BN
+        for wave, lane in itertools.product(range(NW), (0, 7, 8, 63)):
+            for op, n, lim in ((o.x, IA, (m0, M)), (o.w, IB, (n0, N))):
+                for i in range(n):
+                    r = (wave * n + i) * RPI + lane // CPR
+                    c = (lane % CPR) ^ plan().lp_gemm_swz(tile, r)
+                    for kt in {0, K // BK - 1}:
+                        op(min(lim[0] + r, lim[1] - 1), c * 8 + kt * BK)
+        o.done = set()
+        for wave, lane in itertools.product(range(NW), range(64)):
+            wm, wn = wave % (BM // WM), wave // (BM // WM)
+            for i, j in itertools.product(range(WM // 16), range(WN // 16)):
+                m = m0 + wm * WM + i * 16 + (lane & 15)
+                if m < M:
+                    o.out4(m, n0 + wn * WN + j * 16 + 4 * (lane >> 4))
+        assert len(o.done) == (min(m0 + BM, M) - m0) * (min(n0 + BN, N) - n0)
+
+
+def _linear_ranges(M, N, K, ldx, ldy, n2, ns, split, f32):
+    """Operand ranges of the kernel that the host picks for a map without LayerNorm."""
+    o = _Map(M, N, K, ldx, ldy, n2, ns, split)
+    if f32 and plan().lp_wide_fits(M, N, K):
+        _wide_range(o)
+    elif M <= 128:
+        _few_range(o)
+    else:
+        _gemm_range(o)
+    return o.hi
+
+
+@pytest.mark.parametrize("d,vocab,rows", [(128, 256, 448), (768, 1000, 130), (2048, 77, 64), (256, 300, 100),
+                                         (768, 50257, 64), (1024, 4000, 4096), (832, 300, 256), (2048, 300, 256),
+                                         (2048, 50257, 520), (2048, 50257, 136), (2048, 50257, 1), (832, 1000, 200),
+                                         (1024, 9001, 17), (1088, 12001, 48), (1984, 12001, 128), (64, 8192, 33),
+                                         (1216, 9000, 1300), (2048, 50257, 32)])
+def test_model_kernel_indexing(d, vocab, rows):
+    """Every linear-map launch the model makes stays inside its operands (x
+    [rows, K] in a [max_tokens, ldx] buffer, W [N or n2, K] and [N - n2, K],
+    y [rows, ldy]); LayerNorm and embedding lanes stay inside a d-wide row."""
+    calls = [  # M, N, K, ldx, ldy, n2, ns, split, rows of W (first, second), fp32
+        (rows, 3 * d, d, d, d, 3 * d, d, True, 3 * d, 0, False),        # qkv, split into q, k, v
+        (rows, d, d, d, d, d, 0, False, d, 0, False),                   # attention out (+ residual)
+        (rows, 4 * d, d, d, 4 * d, 4 * d, 0, False, 4 * d, 0, False),   # ffn up
+        (rows, d, 4 * d, 4 * d, d, d, 0, False, d, 0, False),           # ffn down (+ residual)
+        (rows, 2 * d, d, d, d, d, d, True, d, d, False),                # memory K | V maps
+        (1, 2 * d, d, d, 2 * d, d, 0, False, d, d, False),              # null row through K | V
+        (rows, vocab, d, d, vocab, vocab, 0, False, vocab, 0, True),    # output head (fp32)
+    ]
+    for M, N, K, ldx, ldy, n2, ns, split, wrows, w2rows, f32 in calls:
+        assert K % 64 == 0 and K <= ldx
+        hi = _linear_ranges(M, N, K, ldx, ldy, n2, ns, split, f32)
+        assert hi["x"] < M * ldx
+        assert hi["w"] < wrows * K
+        assert hi["w2"] < max(w2rows, 0) * K or hi["w2"] == -1
+        assert hi["y"] < (M * ns if split else M * ldy)
+    # embedding: lane chunks c = i*512 + 8*lane (i < 4) guarded by c < d, 8 values each
+    assert d % 8 == 0 and d <= 2048
+    for i, lane in itertools.product(range(4), range(64)):
+        c = i * 512 + lane * 8
+        if c < d:
+            assert c + 7 < d
+    assert 3 * 512 + 63 * 8 + 8 >= 2048         # the four chunks cover d = 2048
 
 
 def test_few_row_launches_fit():
@@ -525,20 +583,17 @@ def test_gemm_tile_rule_picks_a_fast_tile(shape):
     assert us[gemm_tile(*shape)] <= 1.05 * min(us), (gemm_tile(*shape), us)
 
 
-@pytest.mark.parametrize("BM,BN,NS,WAVES_M,WAVES_N", [(128, 256, 3, 2, 4), (128, 128, 4, 2, 4), (128, 128, 2, 2, 2),
-                                                        (64, 64, 4, 2, 2), (64, 64, 2, 2, 2)])
-def test_gemm_stage_layout(BM, BN, NS, WAVES_M, WAVES_N):
+@pytest.mark.parametrize("tile", range(5), ids=["wide", "tall", "pair", "small", "brief"])
+def test_gemm_stage_layout(tile):
     """k_gemm's stage in LDS: the DMA instructions of the waves write every
     16-byte slot of it once, from inside the tile's rows, and each operand
     read (one lane address per operand, the second 32-wide step's slots those
     of the first with bit 2 flipped, tiles of 16 rows at fixed offsets) finds
     the chunk of its row and step."""
-    BK, CPR, RPI, R256 = 64, 8, 8, 2
-    NW = WAVES_M * WAVES_N
-    WM, WN = BM // WAVES_M, BN // WAVES_N
-    IA, IB, STAGE = BM // RPI // NW, BN // RPI // NW, (BM + BN) * BK
-    assert NS * STAGE * 2 <= 160 * 1024 and IA * RPI * NW == BM and IB * RPI * NW == BN
-    swz = lambda r: (r // R256) % CPR
+    BM, BN, BK, NS, NW, WM, WN, IA, IB, RPI, CPR, STAGE, PER = _ints(plan().lp_gemm_cfg, 13, tile)
+    WAVES_M = BM // WM
+    assert BK == 64 and NS * STAGE * 2 * PER <= 160 * 1024 and IA * RPI * NW == BM and IB * RPI * NW == BN
+    swz = lambda r: plan().lp_gemm_swz(tile, r)
     slots = {}                                     # element offset of a 16-byte slot -> (operand, row, chunk)
     for wave, lane in itertools.product(range(NW), range(64)):
         for op, n, base in (("x", IA, 0), ("w", IB, BM * BK)):
@@ -563,8 +618,7 @@ def test_few_row_tile_layout():
     writes fill 8 KB once, operand reads of step t find chunk 4 t + l / 16 of
     row l % 16, and the 16 rows of one read lie in 16 different 16-byte
     columns of the banks."""
-    put = lambda r, s: r * 512 + ((s ^ r) << 4)
-    get = lambda lane, t: (lane & 15) * 512 + (((t * 4 + (lane >> 4)) ^ (lane & 15)) << 4)
+    put, get = plan().lp_few_put, plan().lp_few_get
     at = {}
     for i, lane in itertools.product(range(8), range(64)):
         r, s = 2 * i + (lane >> 5), lane & 31
@@ -614,90 +668,139 @@ def test_layernorm_tree_is_one_order(R):
     assert {add(z[g], z[g ^ 1]) for g in range(4)} == {want}
 
 
-def _ln_groups_rows(d, rows=5):
-    """k_ln_rows: the (chunk, group) partial each active lane sums, as the
-    ordered k list it reads; every row of a wave (and of the last, partial
-    wave) sees the same partials, and its shuffles stay inside its lanes."""
-    KS, NC = d // 32, (d // 32 + 7) // 8
-    LPR = 4 * NC
-    R = 64 // LPR                                   # ln_rows_per_wave
-    assert NC <= 8 and R >= 2
-    per_row = {}
-    for blk in range(-(-rows // R)):
-        for lane in range(64):
-            rl = lane // LPR
-            base, l = rl * LPR, lane - rl * LPR
-            row = blk * R + rl
-            if rl >= R or row >= rows:
-                continue
-            c, g = l >> 2, l & 3
-            for o in (1, 2):                        # xor partners: the same row, the same chunk
-                assert (lane ^ o) // LPR == rl and ((lane ^ o) - base) >> 2 == c
-            assert all(base + 4 * q < base + LPR for q in range(NC))
-            nt = min(8, KS - 8 * c)
-            k0 = 256 * c + 8 * g
-            per_row.setdefault(row, {})[(c, g)] = [k0 + 32 * t + e for t in range(nt) for e in range(8)]
-    assert sorted(per_row) == list(range(rows))
-    first = per_row[0]
-    assert all(v == first for v in per_row.values())
-    return first
+def _ln_rows_pieces(d, rows):
+    """k_ln_rows: the 8-value pieces of a row by (chunk, piece), from the lanes
+    that load them (a wave per row, a half-wave per chunk of 256, up to four
+    chunks per half-wave); every load and store inside the row."""
+    NC = (d + 255) // 256
+    assert NC <= 8
+    seen = {}
+    for blk, tid in itertools.product(range(-(-rows // 4)), range(256)):
+        lane, row = tid & 63, blk * 4 + (tid >> 6)
+        if row >= rows:
+            continue
+        half = lane >> 5
+        k0 = half * 256 + (lane & 31) * 8
+        for i in range(4):
+            if k0 + 512 * i < d:
+                assert k0 + 512 * i + 7 < d
+                # register i of half-wave h holds chunk 2 i + h, which the total takes from lane 32 h
+                seen.setdefault(row, {})[(2 * i + half, lane & 31)] = k0 + 512 * i
+    assert sorted(seen) == list(range(rows)) and all(v == seen[0] for v in seen.values())
+    assert all(c < NC for c, _ in seen[0])     # totals are taken of chunks below NC only
+    return seen[0]
 
 
-def _ln_groups_skinny(d):
-    """k_linear_skinny_ln: the same partials as wave c, lane group g = lane >> 4
-    hold them (steps s0 + t, t < ns, of the wave's chunk)."""
-    KS, NC = d // 32, (d // 32 + 7) // 8
-    out = {}
-    for c in range(NC):
-        s0, ns = 8 * c, min(8, KS - 8 * c)
-        for g in range(4):
-            kofs = 8 * g
-            out[(c, g)] = [(s0 + t) * 32 + kofs + e for t in range(ns) for e in range(8)]
-    return out
+def _few_ln_pieces(M, N, K, kind):
+    """k_linear_few_ln: the same pieces as its waves load them, with every load
+    inside the operands and every LDS access inside its region."""
+    RT, G, WPC, _, threads, lds = _ints(plan().lp_few_ln_plan, 6, kind, K)
+    KS = K // 32
+    NC = (KS + 7) // 8
+    GW, RI = G // WPC, 8 // WPC
+    tiles, st0 = NC * WPC * 8192, NC * WPC * 8192
+    st1 = st0 + 512
+    part = st1 + 512
+    assert part + NC * G * 1024 <= lds and threads == 64 * NC * WPC
+    zeroed = {e for e in range(NC * 16, 128)}  # statistics past the last chunk
+    o = _Map(M, N, K, K, N, N, 0, False)
+    rt, cg = -(-M // 16), -(-N // (16 * G))
+    walk = _walk(rt * cg, rt)
+    pieces, pub = {}, {}
+    for r_t, g in {walk[i] for i in _some(len(walk))} | {(rt - 1, cg - 1)}:
+        m0, n0 = r_t * 16, g * 16 * G
+        for w in range(NC * WPC):
+            c, h = w // WPC, w % WPC
+            nt, k0 = min(8, KS - 8 * c), c * 256
+            assert nt >= 1
+            rows_put = set()
+            for lane in range(64):
+                half, s = lane >> 5, lane & 31
+                in_ = s < 4 * nt
+                q = s if in_ else 0
+                assert k0 + q * 8 + 7 < K             # gain and bias
+                for i in range(RI):
+                    r = h * 2 * RI + 2 * i + half
+                    assert r < 16
+                    o.x(min(m0 + r, M - 1), k0 + q * 8)
+                    if in_ and m0 + r < M:
+                        pieces.setdefault((c, s), set()).add(k0 + q * 8)
+                    at = c * WPC * 8192 + plan().lp_few_put(r, s)
+                    assert at + 16 <= tiles and at not in rows_put
+                    rows_put.add(at)
+                tr = h * 2 * RI + 2 * ((s >> 2) // (8 // RI)) + half
+                if s & 3 == 0:                        # publishes row tr: the tree's row for these lanes
+                    assert tr < 16 and c * 16 + tr < 128
+                    pub.setdefault((c, tr), set()).add(h)
+            for j in range(GW):
+                _few_load(lambda r: min(n0 + (h * GW + j) * 16 + r, N - 1), k0, nt, o.w)
+                for lane in (0, 15, 16, 63):
+                    at = part + ((c * 16 + (lane & 15)) * 16 * G + (h * GW + j) * 16 + 4 * (lane >> 4)) * 4
+                    assert at % 16 == 0 and at + 16 <= part + NC * G * 1024
+            assert w * 8192 + 8192 <= tiles           # the wave's own tile
+        _few_finish(o, 1, G, threads, NC, m0, n0, part, lds)
+    assert set(pub) == {(c, r) for c in range(NC) for r in range(16)} and all(len(v) == 1 for v in pub.values())
+    assert {c * 16 + r for c, r in pub} | zeroed == set(range(128))
+    assert o.hi["x"] < M * K and o.hi["w"] < N * K and o.hi["y"] < M * N
+    return {k: next(iter(v)) for k, v in pieces.items() if len(v) == 1}
 
 
-def skinny_ln_lds(nc, rt, g, K):                   # bytes (linear.h): statistics, then partial sums, in one space
-    return max(nc * 1024 * rt * g, 4 * K + 2 * nc * 16 * rt * 4)
+def _skinny_ln_pieces(M, N, K, kind):
+    """k_linear_skinny_ln: the pieces as wave c, lane group g = lane / 16 hold
+    them (piece 4 t + g of step t), loads and LDS regions inside their bounds."""
+    RT, G, _, U, threads, lds = _ints(plan().lp_few_ln_plan, 6, kind, K)
+    KS = K // 32
+    NC = (KS + 7) // 8
+    assert threads == 64 * NC <= 512 and U <= 8
+    st0 = 4 * K
+    st1 = st0 + NC * 16 * RT * 4
+    assert st0 % 16 == 0 and st1 + NC * 16 * RT * 4 <= lds and NC * 256 * RT * G * 4 <= lds
+    for tid in range(threads):                # gain and bias staging
+        if tid * 8 < K:
+            assert 2 * (K + tid * 8 + 7) < st0
+    assert 8 * threads >= K
+    o = _Map(M, N, K, K, N, N, 0, False)
+    rt, cg = -(-M // (16 * RT)), -(-N // (16 * G))
+    walk = _walk(rt * cg, rt)
+    pieces = {}
+    for r_t, g in {walk[i] for i in _some(len(walk))} | {(rt - 1, cg - 1)}:
+        m0, n0 = r_t * 16 * RT, g * 16 * G
+        for c, lane in itertools.product(range(NC), (0, 15, 16, 32, 48, 63)):
+            s0, ns, kofs = 8 * c, min(8, KS - 8 * c), (lane >> 4) * 8
+            assert ns >= 1
+            for t in range(8):
+                k = (s0 + min(t, ns - 1)) * 32 + kofs
+                for i in range(RT):
+                    o.x(min(m0 + i * 16 + (lane & 15), M - 1), k)
+                for j in range(G):
+                    o.w(min(n0 + j * 16 + (lane & 15), N - 1), k)
+                if t < ns:
+                    pieces[(c, 4 * t + (lane >> 4))] = k
+            for i in range(RT):
+                assert c * 16 * RT + i * 16 + (lane & 15) < NC * 16 * RT
+        _few_finish(o, RT, G, threads, NC, m0, n0, 0, lds)
+    assert o.hi["x"] < M * K and o.hi["w"] < N * K and o.hi["y"] < M * N
+    return pieces
 
 
 @pytest.mark.parametrize("M,N,K", [(64, 3072, 1024), (64, 6144, 2048), (64, 8192, 2048), (64, 1024, 1024),
                                    (128, 3072, 768), (1, 4096, 1024), (33, 4160, 832), (64, 2048, 128),
                                    (64, 2496, 832), (64, 3328, 832), (64, 832, 832), (16, 6144, 2048),
-                                   (16, 8192, 2048)])
+                                   (16, 8192, 2048), (1, 36, 64), (128, 4096, 64), (15, 100, 320), (128, 8192, 512),
+                                   (128, 4096, 1024), (17, 2048, 1088), (70, 6148, 1984), (9, 20000, 1984), (7, 30000, 768)])
 def test_layernorm_fused_indexing_and_order(M, N, K):
-    """The LayerNorm fused into a few-row map and the stand-alone LayerNorm
-    kernel sum every row over the same (chunk, group) partials, each in the
-    same ascending k order, covering the row once; the fused kernel's loads,
-    LDS regions and tile choice stay inside their buffers."""
-    rows, sk = _ln_groups_rows(K), _ln_groups_skinny(K)
-    assert rows == sk
-    allk = sorted(k for ks in sk.values() for k in ks)
-    assert allk == list(range(K))
-    NC = (K + 255) // 256
-    fits = lambda rt, g: (-(-M // (16 * rt)) * -(-N // (16 * g)) >= 192
-                          and skinny_ln_lds(NC, rt, g, K) <= 65536 and (rt == 1 or M > 16))
-    order = ((1, 2), (2, 4), (2, 2), (1, 2), (1, 1)) if K <= 1024 else ((2, 4), (2, 2), (1, 2), (1, 1))
-    RT, G = next(c for c in order if c == (1, 1) or fits(*c))
-    lds = skinny_ln_lds(NC, RT, G, K)
-    assert lds <= 65536 and 64 * NC <= 512          # __launch_bounds__(512)
-    part, gb0 = NC * 256 * RT * G * 4, 0              # gain/bias/statistics until the MFMAs, then partial sums
-    st0 = gb0 + 4 * K
-    st1 = st0 + NC * 16 * RT * 4
-    assert st0 % 16 == 0 and st1 + NC * 16 * RT * 4 <= lds and part <= lds
-    for tid in range(64 * NC):                      # gain / bias staging
-        q8 = tid * 8
-        if q8 < K:
-            assert gb0 + 2 * (K + q8 + 7) < st0
-    assert 8 * 64 * NC >= K
-    for c, lane in itertools.product(range(NC), (0, 15, 16, 63)):
-        KS = K // 32
-        s0, ns = 8 * c, min(8, KS - 8 * c)
-        assert ns >= 1
-        for t in range(8):                          # x, W and gain loads at the clamped step
-            k = (s0 + min(t, ns - 1)) * 32 + (lane >> 4) * 8
-            assert k + 7 < K
-        for i in range(RT):                         # statistics slots
-            assert c * 16 * RT + i * 16 + (lane & 15) < NC * 16 * RT
+    """The LayerNorm fused into a few-row map and the stand-alone kernel cut
+    every row into the same (chunk, piece) values, covering it once (the tree
+    that adds the pieces is one order in all of them:
+    test_layernorm_tree_is_one_order); loads, LDS regions and stores of the
+    kernel that the host picks stay inside their buffers."""
+    want = _ln_rows_pieces(K, 5)
+    assert sorted(k + e for k in want.values() for e in range(8)) == list(range(K))
+    assert all(k == c * 256 + p * 8 for (c, p), k in want.items())
+    kind = plan().lp_few_ln_kind(M, N, K)
+    wpc = _ints(plan().lp_few_ln_plan, 6, kind, K)[2]
+    got = _few_ln_pieces(M, N, K, kind) if wpc else _skinny_ln_pieces(M, N, K, kind)
+    assert got == want
 
 
 def test_gelu_erf_formula_in_source():
