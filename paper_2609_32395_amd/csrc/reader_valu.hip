@@ -398,13 +398,15 @@ static hipError_t launch_rv(const ReaderArgs& a, hipStream_t s) {
   // rotary phases 41.6 against 32.3 (2 blocks of 8 heads).
   using C = RCfg<T, DH, B>;
   constexpr int loads = C::KLOADS + C::VLOADS;
-  if (max_split > 0 && max_split <= (loads > 32 ? 0 : DH == 32 && loads <= 4 ? 2 : 1)) {
-    grid.y = 1;
-    if (a.rope != nullptr)
-      hipLaunchKernelGGL((k_reader_valu<T, DH, B, true, true, true>), grid, dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL((k_reader_valu<T, DH, B, false, true, true>), grid, dim3(256), 0, s, a);
-    return hipGetLastError();
+  if constexpr (loads <= 32) {
+    if (max_split > 0 && max_split <= (DH == 32 && loads <= 4 ? 2 : 1)) {
+      grid.y = 1;
+      if (a.rope != nullptr)
+        hipLaunchKernelGGL((k_reader_valu<T, DH, B, true, true, true>), grid, dim3(256), 0, s, a);
+      else
+        hipLaunchKernelGGL((k_reader_valu<T, DH, B, false, true, true>), grid, dim3(256), 0, s, a);
+      return hipGetLastError();
+    }
   }
   if (a.rope != nullptr)
     hipLaunchKernelGGL((k_reader_valu<T, DH, B, true>), grid, dim3(256), 0, s, a);

@@ -46,3 +46,12 @@ def test_encoder_waves_per_simd():
     assert len(enc) == 12
     for name, res in enc.items():
         assert res["Occupancy [waves/SIMD]"] >= 4, (name, res)
+
+
+def test_reader_folds_only_what_a_launch_reaches():
+    """The folding reader is built for pages of at most 32 loads per lane, the
+    ones its launch rule accepts: not for fp32 heads of 128 in 64-row pages."""
+    ks = _resource_remarks(os.path.join(B.CSRC, "reader_valu.hip"))
+    fold = [n for n in ks if re.search(r"k_reader_valuI[ft]Li\d+ELi\d+ELb[01]ELb1ELb1E", n)]
+    assert len(fold) == 2 * (2 * 3 * 2 - 1)      # rotary or not; types x widths x blocks but that one
+    assert not [n for n in fold if "IfLi128ELi64E" in n]
