@@ -388,18 +388,25 @@ static hipError_t launch_rv(const ReaderArgs& a, hipStream_t s) {
   }
   dim3 grid(a.H, max_split + 1, a.n_slots * a.nq);
   // One workgroup per (query, head) folds one memory split with the null row
-  // and in-block keys where a page is at most 32 loads per lane, or two splits
-  // (of 4 pages) of blocks of 16 with heads of 32: a phase more costs less than
-  // the merge's launch.  Us per call, folded against split + merge: decode of 64
+  // and in-block keys where a page is at most 32 loads per lane: a phase more
+  // costs less than the merge's launch.  Two splits (of 4 pages) of blocks of 16
+  // with heads of 32 as well, where the workgroups are neither so few that the
+  // second split's wait is all that runs (decode; a query block's workgroups
+  // share their pages) nor so many that the split launch fills the chip with
+  // smaller ones.  Us per call, folded against split + merge: decode of 64
   // sequences, 16 heads of 64 over 3 / 8 pages 16.6 / 29.4 against 20.3 / 34.7,
-  // two splits of 64-row pages 51.6 against 47.7; prefill of a block of 16 over
-  // two splits, 4 heads of 32 6.0 against 6.4, 8 heads of 64 7.8 against 7.3;
-  // fp32 heads of 128, 64-row pages (64 loads per lane) 12.7 against 11.3, with
-  // rotary phases 41.6 against 32.3 (2 blocks of 8 heads).
+  // two splits of 64-row pages 51.6 against 47.7; two splits of 16-row pages,
+  // folded over split + merge at 16 / 256 / 1024 / 2048 / 4096 workgroups: decode
+  // 1.01 / 0.93 / 0.80 / 0.95 / 1.03, prefill of whole blocks 0.97 / 0.89 / 0.80 /
+  // 0.85 / 0.91 (fp32, 16 heads: 1.03), 8192 0.98, 16384 1.01; with heads of 64
+  // 7.8 against 7.3; fp32 heads of 128, 64-row pages (64 loads per lane) 12.7
+  // against 11.3, with rotary phases 41.6 against 32.3 (2 blocks of 8 heads).
   using C = RCfg<T, DH, B>;
   constexpr int loads = C::KLOADS + C::VLOADS;
   if constexpr (loads <= 32) {
-    if (max_split > 0 && max_split <= (DH == 32 && loads <= 4 ? 2 : 1)) {
+    const long wgs = (long)a.H * a.n_slots * a.nq;
+    const bool two = DH == 32 && B == 16 && (a.nq > 1 ? wgs * loads <= 8192 : wgs >= 256 && wgs <= 2048);
+    if (max_split == 1 || (max_split == 2 && two)) {
       grid.y = 1;
       if (a.rope != nullptr)
         hipLaunchKernelGGL((k_reader_valu<T, DH, B, true, true, true>), grid, dim3(256), 0, s, a);

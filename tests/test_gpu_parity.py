@@ -545,8 +545,8 @@ def test_device_copy_both_paths():
         smem.smem_device_copy(torch.zeros(1000, device="cuda"), torch.zeros(1000, device="cuda"), via_lds=True)
 
 
-# A short read (one memory split, or two of blocks of 16 with heads of 32; not
-# fp32 heads of 128 in 64-row pages) is folded by one workgroup when every read
+# A short read (one memory split, or two of blocks of 16 with heads of 32 in a
+# prefill; not fp32 heads of 128 in 64-row pages) is folded by one workgroup when every read
 # of its launch is short, and split and merged when
 # a long read shares the launch: the same bits, with and without the null row,
 # in-block keys and rotary phases, in decode and in VALU prefill.
@@ -593,6 +593,43 @@ def test_short_reads_folded_bitwise_split(dtype, b, H, dh, rope):
     both = prefill([0, 1, 2, 3])
     for s in range(3):
         assert torch.equal(prefill([s]), both[s * b:(s + 1) * b]), s
+
+
+# Two memory splits of 16-row blocks with heads of 32 are folded by a launch of
+# 256 to 2048 decode workgroups, or of at most 8192 / loads prefill workgroups,
+# and split and merged by smaller decode calls and larger prefills: the same bits
+# on both sides of each line.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rope", [False, True])
+def test_two_split_reads_bitwise_across_the_rule(dtype, rope):
+    say("two-split reads", dtype, rope)
+    b, H, dh, n, pages = 16, 8, 32, 33, 7
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    r = lambda *s: torch.randn(s, generator=g, device="cuda").to(dtype)
+    st = smem.Store(n, pages, n * pages, b, H, dh, dtype)
+    for s in range(n):
+        smem.smem_store_put_blocks(st, [s] * pages, list(range(pages)), r(pages * b, H, dh), r(pages * b, H, dh))
+    tab = smem.Rope(dh, 64, max_offset=3) if rope else None
+    null, pos = r(2, H, dh), [(5 * s) % b for s in range(n)]
+    q, kn, vn, kc, vc = r(n, H, dh), r(n, H, dh), r(n, H, dh), r(n * b, H, dh), r(n * b, H, dh)
+    Q, K, V = r(n * b, H, dh), r(n * b, H, dh), r(n * b, H, dh)
+
+    def decode(lo, hi):
+        c = lambda x, k=1: x[lo * k:hi * k].clone()
+        a = (list(range(lo, hi)), [pages] * (hi - lo), pos[lo:hi], c(q), c(kn), c(vn), c(kc, b), c(vc, b), null)
+        return smem.smem_reader_decode_rope(st, tab, *a) if rope else smem.smem_reader_decode(st, *a)
+
+    def prefill(lo, hi):
+        c = lambda x: x[lo * b:hi * b].clone()
+        a = (list(range(lo, hi)), [pages] * (hi - lo), c(Q), c(K), c(V), null)
+        return smem.smem_reader_prefill_block_rope(st, tab, *a) if rope else smem.smem_reader_prefill_block(st, *a)
+
+    whole = decode(0, n)                         # 264 workgroups
+    assert torch.equal(decode(0, 31), whole[:31])  # 248
+    whole = prefill(0, n)                        # 4224
+    for lo, hi in ((0, 32), (16, 32), (32, 33)):  # 4096, 2048, 128
+        assert torch.equal(prefill(lo, hi), whole[lo * b:hi * b]), (lo, hi)
 
 
 # Few-pair prefill gives a pair to four workgroups of 16 rows up to 64 pairs and
