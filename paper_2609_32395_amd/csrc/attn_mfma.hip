@@ -64,12 +64,14 @@ __device__ __forceinline__ int xcd_range(int n, int all) {
 // workgroups read neighbouring head slices of the same token rows.  Every
 // tile's loads are issued at once; with all tiles resident, tiles whose data
 // arrive first compute while the rest are still loading.  The tile sits in
-// LDS in the page layout, so the operand reads are the prefill's.  At least
-// four workgroups stay on a CU: with rotary phases at d_h = 128 and the causal
-// mask the free choice is 131 registers, one workgroup fewer than 128 allow
-// (64 blocks of 32 heads 31.9 us on three, 28.3 on four).
+// LDS in the page layout, so the operand reads are the prefill's.  With rotary
+// phases at d_h = 128 and the causal mask the registers' free choice is 131,
+// which leaves three workgroups on a CU instead of four (64 blocks of 32 heads
+// 31.9 us on three, 28.3 on four): that one is asked for four, the others take
+// what they choose.
 template <int DH, bool CAUSAL, bool ROPE>
-__global__ void __launch_bounds__(256, 4) k_encoder_mfma(EncArgs a) {
+__global__ void __launch_bounds__(256, DH == 128 && CAUSAL && ROPE ? 4 : 1)
+    k_encoder_mfma(EncArgs a) {
   using R = PageRing<DH>;
   __shared__ __attribute__((aligned(1024))) uint8_t T[R::TILE];
   int h = blockIdx.x, blk = blockIdx.y;
