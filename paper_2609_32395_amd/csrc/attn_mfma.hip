@@ -53,13 +53,6 @@ struct EncArgs {
   int32_t sink[kMaxSlots];   // page of block i, or -1
 };
 
-// Tile of workgroup n of `all` when each XCD (workgroup index mod 8) takes a
-// contiguous range of them: a permutation of 0 .. all - 1.
-__device__ __forceinline__ int xcd_range(int n, int all) {
-  const int x = n & 7, more = all & 7;
-  return x * (all >> 3) + (x < more ? x : more) + (n >> 3);
-}
-
 // One workgroup per (block, head) tile, heads fastest: neighbouring
 // workgroups read neighbouring head slices of the same token rows.  Every
 // tile's loads are issued at once; with all tiles resident, tiles whose data
@@ -466,26 +459,6 @@ __device__ __forceinline__ void prefill_body(const ReaderArgs& a, PrefillLds<DH,
 // last, with the merge's functions, each wave one 16-wide dimension tile of
 // its rows: every split is computed as in the split launch and the folding
 // launch, so all three give the same bits.
-template <int DH, int QW>
-struct ParLds {
-  using R = PageRing<DH>;
-  static constexpr int G = 4;                          // split groups
-  static constexpr int NSP = DH == 32 ? 4 : 2;         // ring stages per group
-  static constexpr int IPW = R::TILE / 1024 / QW;      // DMA instructions per wave per page
-  static constexpr int THREADS = 64 * G * QW;
-  static constexpr int ROWS = 16 * QW;                 // query rows per workgroup
-  static constexpr int RING = G * NSP * R::TILE;
-  static constexpr int OFF_IN = RING;                  // in-block tile, ring layout
-  static constexpr int OFF_NULL = OFF_IN + R::TILE;    // null key, then null value (bf16)
-  static constexpr int BYTES = OFF_NULL + 4 * DH;
-  // a split state per (slot, wave): o as DH/16 float4 planes of 64 lanes, then (m, l) pairs;
-  // slots 0..3 hold memory splits 0..3, slot 4 the final split
-  static constexpr int STATE = (DH / 16) * 1024 + 64 * 8;
-  static_assert((G + 1) * QW * STATE <= RING, "split states fit in the ring");
-  static_assert(BYTES <= 160 * 1024, "LDS");
-  static_assert(NSP >= 2 && NSP <= 4 && 3 * IPW < 64, "wait_pages covers up to 3 pages ahead");
-};
-
 template <int DH>
 __device__ __forceinline__ void state_put(uint8_t* st, const floatx4 (&o)[DH / 16], float m, float l, int lane) {
 #pragma unroll
@@ -493,18 +466,12 @@ __device__ __forceinline__ void state_put(uint8_t* st, const floatx4 (&o)[DH / 1
   *(f32x2*)(st + (DH / 16) * 1024 + lane * 8) = f32x2{m, l};
 }
 
-// Workgroups of a few-pair launch: 4/QW parts per pair, 8 pairs per round of
-// 8 x (4/QW) launch indices.
-inline int par_grid(int n_pairs, int qw) { return ((n_pairs + 7) / 8) * 8 * (4 / qw); }
-
 template <int DH, int QW>
 __global__ void __launch_bounds__(64 * 4 * QW) k_prefill_mfma_par(ReaderArgs a) {
   using P = ParLds<DH, QW>;
   using R = PageRing<DH>;
-  constexpr int NPART = 4 / QW;
   __shared__ __attribute__((aligned(1024))) uint8_t L[P::BYTES];
-  const int n = blockIdx.x;
-  const int pair = (n / (8 * NPART)) * 8 + (n % 8), part = (n / 8) % NPART;
+  const int pair = par_pair(blockIdx.x, QW), part = par_part(blockIdx.x, QW);
   if (pair >= a.n_slots * a.H) return;   // padding of the last round (whole workgroup)
   const int slot = pair / a.H, h = pair % a.H;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -669,13 +636,12 @@ static hipError_t launch_pre(const ReaderArgs& a, hipStream_t s) {
   }
   if (a.fuse == 2) {
     constexpr int D = DH > 64 ? 64 : DH;                 // (no few-pair variant at d_h 128)
-    if (a.rope || DH > 64 || max_split > ParLds<D, 4>::G) return hipErrorInvalidValue;
+    if (a.rope || DH > 64 || max_split > kParSplits) return hipErrorInvalidValue;
     const int n_pairs = a.n_slots * a.H;
-    // up to 64 pairs, four workgroups of 16 rows still run one per CU: us per
-    // call over 15 pages on QW 1 / 2: 32 heads of 32, 1 block 6.8 / 7.9, 4 blocks
-    // 12.8 / 9.0; 16 heads of 64, 1 block 8.4 / 9.8; 12 heads, 8 blocks 19.1 / 12.6
-    if (n_pairs <= 64) hipLaunchKernelGGL((k_prefill_mfma_par<D, 1>), dim3(par_grid(n_pairs, 1)), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_prefill_mfma_par<D, 2>), dim3(par_grid(n_pairs, 2)), dim3(512), 0, s, a);
+    if (par_row_waves(n_pairs) == 1)
+      hipLaunchKernelGGL((k_prefill_mfma_par<D, 1>), dim3(par_grid(n_pairs, 1)), dim3(ParLds<D, 1>::THREADS), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_prefill_mfma_par<D, 2>), dim3(par_grid(n_pairs, 2)), dim3(ParLds<D, 2>::THREADS), 0, s, a);
     return hipGetLastError();
   }
   if (a.fuse) {

@@ -6,14 +6,13 @@
 // at the top of attn_mfma.hip.
 #pragma once
 
+#include "attn_plan.h"
 #include "common.h"
 
 namespace smem {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef f32x4 floatx4;
-
-constexpr int BT = 64;         // block / page size handled here
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 u) {
   bf16x8 r;
@@ -95,12 +94,6 @@ __device__ __forceinline__ float qmax(float x) { return xor32_op_max(xor16_op_ma
 __device__ __forceinline__ float qsum(float x) { return xor32_op_sum(xor16_op_sum(x)); }
 
 
-// The key of a 64-key tile that a lane's score s[kt][i] belongs to, less the
-// lane's own part 8 (lane / 16): the two 16-row score tiles of 32 keys
-// interleave by fours (tile_row below), so the lane's scores of tiles 2c and
-// 2c + 1 are 8 consecutive keys.
-__device__ constexpr int score_key(int kt, int i) { return (kt >> 1) * 32 + (kt & 1) * 4 + i; }
-
 // One online-softmax step over a 64-key tile for the lane's query.
 template <int DH, bool CAUSAL>
 __device__ __forceinline__ void online_step(floatx4 (&s)[4], float& m, float& l, floatx4 (&o)[DH / 16], int lane,
@@ -155,68 +148,6 @@ __device__ __forceinline__ void online_step(floatx4 (&s)[4], float& m, float& l,
   l = __builtin_fmaf(l, alpha, ps);
 }
 
-// ------------------------------------------------------------------ LDS tile layout
-
-// A 64-key tile in LDS -- a memory page's (page, head) tile, or a block's own
-// keys and values -- keeps the page layout: the key plane [b][d_h] followed by
-// the transposed value plane [d_h][b], with the 16-byte slots of each row
-// permuted (key row r: slot = chunk ^ kswz(r); value row d: slot = chunk ^
-// vswz(d)), so the rows one MFMA operand read touches fall on distinct banks
-// (measured on gfx950: no bank conflicts for the key and value operand reads).
-// The key rows of each 32 are reordered by fours (key 8g + 4h + i in row 16h +
-// 4g + i): a lane's weights of two score tiles then belong to 8 consecutive
-// keys, and its value operand is one 16-byte read where it was two of 8.
-// Memory pages of the non-rotary prefill move global -> LDS by DMA
-// (global_load_lds_dwordx4, 16 bytes per lane) through a ring of NS page
-// stages, so NS - 1 pages are in flight while one is read and no register
-// holds a page in transit.
-#ifndef SMEM_PREFILL_STAGES32
-#define SMEM_PREFILL_STAGES32 4
-#endif
-#ifndef SMEM_PREFILL_STAGES64
-#define SMEM_PREFILL_STAGES64 4
-#endif
-#ifndef SMEM_PREFILL_STAGES128
-#define SMEM_PREFILL_STAGES128 2
-#endif
-template <int DH>
-struct PageRing {
-  static constexpr int TILE = 2 * BT * DH * 2;         // bytes per (page, head)
-  static constexpr int KBYTES = BT * DH * 2;           // key plane bytes
-  static constexpr int KRB = DH * 2;                   // key row bytes
-  static constexpr int KCH = DH / 8;                   // 16-byte chunks per key row
-  static constexpr int NS = DH == 32 ? SMEM_PREFILL_STAGES32 : DH == 64 ? SMEM_PREFILL_STAGES64 : SMEM_PREFILL_STAGES128;
-  static constexpr int IPW = TILE / 1024 / 4;          // DMA instructions per wave per page
-  static_assert(NS >= 2 && NS <= 5, "wait_pages covers up to 3 pages ahead");
-  // key rows: slot = chunk ^ kswz(r).  Chosen by measurement (a one-wave LDS
-  // bank probe of the score reads): r / 2 for 64-byte rows (r / 4 left them
-  // 2-way conflicted), r / 2 for 128-byte rows, r for 256-byte rows.
-  __device__ static constexpr int kswz(int r) { return (DH == 32 ? r / 2 : r / (256 / KRB)) % KCH; }
-  // value rows: 16 rows of 128 bytes per operand read, as the keys at d_h = 64.
-  // At d_h = 128 the row group is added: a block's own values are written 16
-  // chunks of a row pair at a time, which d / 2 alone puts on two slots (8
-  // ways; encoder, 30 blocks of 20 heads 8.6 us against 8.9).  Below that one
-  // operand address for all row groups is worth more (d_h 64, 128 blocks of
-  // 12 heads: 9.2 us against 9.6).
-  __device__ static constexpr int vswz(int d) { return ((d >> 1) ^ (DH == 128 ? d >> 4 : 0)) & 7; }
-  // LDS row of a key of the tile, and the key in an LDS row
-  __device__ static constexpr int tile_row(int key) {
-    return (key & ~31) + ((key >> 2) & 1) * 16 + ((key >> 3) & 3) * 4 + (key & 3);
-  }
-  __device__ static constexpr int row_key(int row) {
-    return (row & ~31) + ((row >> 2) & 3) * 8 + ((row >> 4) & 1) * 4 + (row & 3);
-  }
-  // Byte of the (page, head) tile in memory that LDS byte `byte` holds.
-  __device__ static int source(int byte) {
-    if (byte < KBYTES) {
-      const int r = byte / KRB, sl = (byte % KRB) >> 4;
-      return row_key(r) * KRB + ((sl ^ kswz(r)) << 4);
-    }
-    const int vb = byte - KBYTES, d = vb >> 7, sl = (vb & 127) >> 4;
-    return KBYTES + d * 128 + ((sl ^ vswz(d)) << 4);
-  }
-};
-
 // S^T for this wave's 16 queries against the 64 keys of a tile.
 template <int DH>
 __device__ __forceinline__ void scores_ring(floatx4 (&s)[4], const uint8_t* tile, const bf16x8 (&qf)[DH / 32],
@@ -229,7 +160,7 @@ __device__ __forceinline__ void scores_ring(floatx4 (&s)[4], const uint8_t* tile
 #pragma unroll
     for (int kk = 0; kk < DH / 32; ++kk) {
       const int c = kk * 4 + (lane >> 4);
-      const u32x4 kf = *(const u32x4*)(tile + r * R::KRB + ((c ^ R::kswz(r)) << 4));
+      const u32x4 kf = *(const u32x4*)(tile + R::key_at(r, c));
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kf), qf[kk], acc, 0, 0, 0);
     }
     s[kt] = acc;
@@ -244,12 +175,11 @@ __device__ __forceinline__ void pv_ring(floatx4 (&o)[DH / 16], const uint8_t* ti
   using R = PageRing<DH>;
   const bf16x8 p0 = pack_p(p[0], p[1]);
   const bf16x8 p1 = pack_p(p[2], p[3]);
-  const int off = R::KBYTES + (lane & 15) * 128 + (((lane >> 4) ^ R::vswz(lane & 15)) << 4);
+  const int off = R::operand_lane(lane);
 #pragma unroll
   for (int dt = 0; dt < DH / 16; ++dt) {
-    const int at = off ^ (R::vswz(dt * 16) << 4);
-    const u32x4 a0 = *(const u32x4*)(tile + at + dt * 2048);
-    const u32x4 a1 = *(const u32x4*)(tile + (at ^ 64) + dt * 2048);
+    const u32x4 a0 = *(const u32x4*)(tile + R::operand_at(off, dt, 0));
+    const u32x4 a1 = *(const u32x4*)(tile + R::operand_at(off, dt, 1));
     o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a0), p0, o[dt], 0, 0, 0);
     o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a1), p1, o[dt], 0, 0, 0);
   }
@@ -292,8 +222,7 @@ __device__ __forceinline__ void intra_ring_store(uint8_t* tile, const uint16_t* 
         rope_turn<8>(x, tab + (size_t)row * DH, c8 * 4);
         kv = pack8(x);
       }
-      const int lr = R::tile_row(row);
-      *(u32x4*)(tile + lr * R::KRB + ((c8 ^ R::kswz(lr)) << 4)) = kv;
+      *(u32x4*)(tile + R::key_at(R::tile_row(row), c8)) = kv;
     } else if (j < NJ) {
       const int pr = (j - NK) / CPR, c8 = (j - NK) % CPR;
       const uint32_t a4[4] = {ra[it].x, ra[it].y, ra[it].z, ra[it].w};
@@ -309,8 +238,7 @@ __device__ __forceinline__ void intra_ring_store(uint8_t* tile, const uint16_t* 
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
           const int dd = d + (k ^ flip);
-          *(uint32_t*)(tile + R::KBYTES + dd * 128 + (key & 7) * 2 + (((key >> 3) ^ R::vswz(dd)) << 4)) =
-              (k ^ flip) ? hi : lo;
+          *(uint32_t*)(tile + R::value_at(dd, key)) = (k ^ flip) ? hi : lo;
         }
       }
     }

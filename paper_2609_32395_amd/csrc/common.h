@@ -82,7 +82,6 @@ inline bool fold_in_workgroup(long n_pairs, int max_pages, int dh) {
 #define SMEM_PAR_PAIRS 128
 #endif
 constexpr int kParPairs = SMEM_PAR_PAIRS;
-constexpr int kParSplits = 4;
 // Query slots whose prefill partials the workspace must hold at once.
 constexpr int kPrefillSlotChunk = 16;
 // Row-plane decode: pages per split max(kMinPagesRows, ceil(n_read /

@@ -18,6 +18,7 @@
 #include <string>
 #include <vector>
 
+#include "attn_plan.h"
 #include "common.h"
 #include "smem.h"
 

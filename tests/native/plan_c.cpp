@@ -1,5 +1,6 @@
-// The library's own linear-map plan (csrc/linear_plan.h) behind C functions,
-// for the index tests.
+// The library's own plans (csrc/linear_plan.h, csrc/attn_plan.h) behind C
+// functions, for the index tests.
+#include "attn_plan.h"
 #include "linear_plan.h"
 
 using namespace smem;
@@ -9,6 +10,17 @@ template <class C>
 void cfg(int* o) {
   const int v[] = {C::BM, C::BN, C::BK, C::NS, C::NW, C::WM, C::WN, C::IA, C::IB, C::RPI, C::CPR, C::STAGE, C::PER_CU};
   for (int i = 0; i < 13; ++i) o[i] = v[i];
+}
+
+// F applied to the tile of a head width
+template <class F>
+int of_width(int dh, F f) {
+  return dh == 32 ? f(PageRing<32>()) : dh == 64 ? f(PageRing<64>()) : f(PageRing<128>());
+}
+template <class P>
+void par(int* o) {
+  const int v[] = {P::G, P::NSP, P::IPW, P::THREADS, P::ROWS, P::RING, P::OFF_IN, P::OFF_NULL, P::BYTES, P::STATE};
+  for (int i = 0; i < 10; ++i) o[i] = v[i];
 }
 }  // namespace
 
@@ -56,4 +68,30 @@ int lp_gemm_place(int i, int tiles_m, int tiles_n) {   // row tile * tiles_n + c
   return p.ok ? p.tm * tiles_n + p.tn : -1;
 }
 int lp_gemm_grid(int per_cu, int T) { return gemm_grid(per_cu, T); }
+
+int ap_score_key(int kt, int i) { return score_key(kt, i); }
+int ap_xcd_range(int n, int all) { return xcd_range(n, all); }
+void ap_ring(int dh, int* o) {                 // tile bytes, key plane bytes, key row bytes, stages, instructions per wave
+  of_width(dh, [&](auto r) {
+    using R = decltype(r);
+    const int v[] = {R::TILE, R::KBYTES, R::KRB, R::NS, R::IPW};
+    for (int i = 0; i < 5; ++i) o[i] = v[i];
+    return 0;
+  });
+}
+int ap_tile_row(int key) { return PageRing<32>::tile_row(key); }
+int ap_source(int dh, int byte) { return of_width(dh, [&](auto r) { return decltype(r)::source(byte); }); }
+int ap_key_at(int dh, int row, int c) { return of_width(dh, [&](auto r) { return decltype(r)::key_at(row, c); }); }
+int ap_value_at(int dh, int d, int key) { return of_width(dh, [&](auto r) { return decltype(r)::value_at(d, key); }); }
+int ap_operand_at(int dh, int lane, int dt, int c) {
+  return of_width(dh, [&](auto r) { return decltype(r)::operand_at(decltype(r)::operand_lane(lane), dt, c); });
+}
+int ap_par_row_waves(int n_pairs) { return par_row_waves(n_pairs); }
+int ap_par_grid(int n_pairs, int qw) { return par_grid(n_pairs, qw); }
+int ap_par_pair(int n, int qw) { return par_pair(n, qw); }
+int ap_par_part(int n, int qw) { return par_part(n, qw); }
+void ap_par(int dh, int qw, int* o) {          // groups, stages, instructions, threads, rows, LDS offsets, state bytes
+  if (dh == 32) qw == 1 ? par<ParLds<32, 1>>(o) : par<ParLds<32, 2>>(o);
+  else qw == 1 ? par<ParLds<64, 1>>(o) : par<ParLds<64, 2>>(o);
+}
 }

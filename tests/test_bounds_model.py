@@ -81,35 +81,11 @@ def test_reader_valu_indexing(b, dh, es):
 @pytest.mark.parametrize("dh", [32, 64, 128])
 def test_mfma_indexing(dh):
     BT = 64
-    KS, VS = dh + 8, BT + 4
-    # transposed-value rows are 8-byte aligned (u32x2 stores and reads), key rows 16-byte aligned
-    assert (VS * 2) % 8 == 0 and (KS * 2) % 16 == 0
-    # bank spread: 16 consecutive value rows (8-byte reads), 8 consecutive key rows (16-byte reads)
-    assert len({(VS * 2 // 4 * r) % 32 for r in range(16)}) == 16
-    assert len({(KS * 2 // 4 * r) % 32 for r in range(8)}) == 8
     # in-block transpose: (row pair, chunk) jobs cover 64 rows x dh, each writes dims c8*8..+7 at rows 2p, 2p+1
     NP = 32 * (dh // 8)
     CPR = dh // 8
     jobs = [((j // CPR), (j % CPR)) for j in range(NP)]       # (row pair, chunk): chunks of a pair adjacent
     assert len(set(jobs)) == NP and max(p for p, _ in jobs) == 31 and max(c for _, c in jobs) * 8 + 7 < dh
-    assert (dh - 1) * VS + 2 * 31 + 1 < dh * VS
-    NK = BT * dh // 8 // 256
-    NV = dh * BT // 8 // 256
-    assert NK * 256 * 8 == BT * dh and NV * 256 * 8 == dh * BT
-    # page tile loads: chunk c = tid + i*256 < NK*256, 8 elements each, inside the (page, head) run
-    assert (255 + (NK - 1) * 256) * 8 + 7 < BT * dh
-    assert BT * dh + (255 + (NV - 1) * 256) * 8 + 7 < 2 * BT * dh
-    # LDS tile stores: key row = c / (dh/8) < 64, column c8*8 + 7 < dh
-    c = 255 + (NK - 1) * 256
-    assert c // (dh // 8) < BT and (c % (dh // 8)) * 8 + 7 < dh
-    c = 255 + (NV - 1) * 256
-    assert c // (BT // 8) < dh and (c % (BT // 8)) * 8 + 7 < BT
-    # LDS operand reads: key tile row kt*16 + 15 < 64, column kk*32 + 3*8 + 7 < dh
-    assert (3 * 16 + 15) < BT and (dh // 32 - 1) * 32 + 3 * 8 + 7 < dh
-    # transposed values: row dt*16 + 15 < dh, columns g*4 + {0,16,32,48} + 3 < 64
-    assert (dh // 16 - 1) * 16 + 15 < dh and 3 * 4 + 48 + 3 < BT
-    # LDS footprint (one buffer) fits the 64 KiB per-workgroup limit
-    assert (BT * KS + dh * VS) * 2 <= 64 * 1024
     # prefill partials: at most 32 splits (split 0 also reads the in-block tile) inside the 65-wide stride
     for n_read in (0, 1, 4, 5, 512, 4096, 65536):
         for H in (1, 12, 16, 24, 32, 64, 600):
@@ -184,10 +160,9 @@ def test_rope_prefill_lds_rows(dh):
             assert n4 * 4 <= ROWS * dh
             assert d_lo * dh + n4 * 4 <= n_phases * dh
             assert all((x - d_lo) * dh + dh <= ROWS * dh for x in d)
-    # LDS per workgroup: max(in-block tiles, page ring) + rows; two workgroups per CU
-    tiles = (64 * (dh + 8) + dh * (64 + 4)) * 2
-    ring = {32: 4, 64: 4, 128: 2}[dh] * 2 * 64 * dh * 2
-    assert 2 * (max(tiles, ring) + ROWS * dh * 4) <= 160 * 1024
+    # LDS per workgroup: the page ring (its first stage takes the in-block tile) + rows; two workgroups per CU
+    tile, _, _, ns, _ = _ints(plan().ap_ring, 5, dh)
+    assert 2 * (ns * tile + ROWS * dh * 4) <= 160 * 1024
 
 
 def _pps_rows(n):
@@ -253,12 +228,12 @@ def test_rows_reader_indexing(b, D):
 
 @functools.lru_cache(None)
 def plan():
-    """The library's own linear-map plan, compiled from its header."""
+    """The library's own plans, compiled from their headers."""
     here = os.path.dirname(os.path.abspath(__file__))
-    out = os.path.join(tempfile.mkdtemp(), "linear_plan.so")
+    out = os.path.join(tempfile.mkdtemp(), "plan.so")
     csrc = os.path.join(here, "..", "paper_2609_32395_amd", "csrc")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", csrc,
-                    os.path.join(here, "native", "linear_plan_c.cpp"), "-o", out], check=True)
+                    os.path.join(here, "native", "plan_c.cpp"), "-o", out], check=True)
     return ctypes.CDLL(out)
 
 
@@ -829,86 +804,99 @@ def test_gelu_erf_formula_in_source():
         assert np.max(np.abs(y[::50] - ref)) <= bound, dt
 
 
-@pytest.mark.parametrize("dh", [32, 64, 128])
-def test_attention_tile_key_order(dh):
-    """The 64-key tile in LDS with its key rows reordered by fours: the DMA's
-    source bytes are a permutation of the (page, head) tile; a lane's scores
-    s[kt][i] belong to the keys that the causal mask assumes, and the 8 slots
-    of its value operand c are the keys of its weights of score tiles 2c and
-    2c + 1, one 16-byte chunk of the transposed value row."""
-    BT, KRB, KB, KCH = 64, dh * 2, 64 * dh * 2, dh // 8
-    kswz = lambda r: ((r // 2) if dh == 32 else (r // (256 // KRB))) % KCH
-    vswz = lambda d: ((d >> 1) ^ (d >> 4 if dh == 128 else 0)) & 7
-    tile_row = lambda k: (k & ~31) + ((k >> 2) & 1) * 16 + ((k >> 3) & 3) * 4 + (k & 3)
-    row_key = lambda r: (r & ~31) + ((r >> 2) & 3) * 8 + ((r >> 4) & 1) * 4 + (r & 3)
-    assert all(row_key(tile_row(k)) == k and tile_row(row_key(k)) == k for k in range(BT))
-
-    def source(byte):
-        if byte < KB:
-            r, sl = byte // KRB, (byte % KRB) >> 4
-            return row_key(r) * KRB + ((sl ^ kswz(r)) << 4)
-        d, sl = (byte - KB) >> 7, ((byte - KB) & 127) >> 4
-        return KB + d * 128 + ((sl ^ vswz(d)) << 4)
-
-    src = {b: source(b) for b in range(0, 2 * KB, 16)}
-    assert sorted(src.values()) == list(range(0, 2 * KB, 16))
-    key_of = lambda kt, i, lane: (kt >> 1) * 32 + (lane >> 4) * 8 + (kt & 1) * 4 + i
+def _tile_reads_find(dh, src):
+    """The score and value operand reads of a 64-key tile whose 16-byte slots
+    (LDS byte -> byte of the (page, head) tile) are `src`: a score row is the key
+    that the causal mask takes it for, and a lane's 8 value slots are the keys of
+    its weights of score tiles 2c and 2c + 1."""
+    _, KB, KRB, _, _ = _ints(plan().ap_ring, 5, dh)
+    key_of = lambda kt, i, lane: plan().ap_score_key(kt, i) + 8 * (lane >> 4)
     for lane in range(64):
         g, l16 = lane >> 4, lane & 15
         for kt, kk in itertools.product(range(4), range(dh // 32)):   # score operand: row kt*16 + l16, chunk kk*4 + g
-            r, c = kt * 16 + l16, kk * 4 + g
-            b = src[r * KRB + ((c ^ kswz(r)) << 4)]
-            assert b == row_key(r) * KRB + c * 16
-            # score row 4 g' + i of tile kt is the key of lane group g', value i
-            assert row_key(r) == key_of(kt, r % 4, (l16 // 4) * 16)
-        off = KB + l16 * 128 + ((g ^ vswz(l16)) << 4)
+            row, c = kt * 16 + l16, kk * 4 + g
+            key, chunk = divmod(src[plan().ap_key_at(dh, row, c)], KRB)
+            assert chunk == c * 16 and key < 64
+            # row 4 g' + i of score tile kt comes out in lane group g', value i
+            assert key == key_of(kt, l16 % 4, (l16 // 4) * 16)
         for dt, c in itertools.product(range(dh // 16), range(2)):
-            b = src[(off ^ (vswz(16 * dt) << 4) ^ (64 * c)) + dt * 2048]
-            first = (b - KB) % 128 // 2
-            assert (b - KB) // 128 == dt * 16 + l16
-            assert [first + j for j in range(8)] == [key_of(2 * c + j // 4, j % 4, lane) for j in range(8)]
+            d, first = divmod(src[plan().ap_operand_at(dh, lane, dt, c)] - KB, 128)
+            assert d == dt * 16 + l16
+            assert [first // 2 + j for j in range(8)] == [key_of(2 * c + j // 4, j % 4, lane) for j in range(8)]
+
+
+@pytest.mark.parametrize("dh", [32, 64, 128])
+def test_attention_tile_key_order(dh):
+    """The DMA's key rows are the keys that the in-block writer puts there: LDS
+    row tile_row(k) holds key k, and the rows are a permutation."""
+    KRB = 2 * dh
+    assert sorted(plan().ap_tile_row(k) for k in range(64)) == list(range(64))
+    for k, c in itertools.product(range(64), range(dh // 8)):
+        assert plan().ap_source(dh, plan().ap_key_at(dh, plan().ap_tile_row(k), c)) == k * KRB + c * 16
 
 
 @pytest.mark.parametrize("dh,ns", [(32, 4), (64, 4), (128, 2)])
 def test_prefill_page_ring_indexing(dh, ns):
     """Non-rotary prefill's DMA page ring: every lane's source byte lies in
     its (page, head) tile, every LDS byte of a stage is written exactly once,
-    and each operand read finds the chunk the DMA put there (key rows and
-    transposed value rows, 16-byte slots permuted per row; key slot = chunk
-    ^ (r / 2) for 64- and 128-byte rows, chunk ^ r for 256-byte rows)."""
-    BT = 64
-    TILE, KBYTES, KRB, KCH = 2 * BT * dh * 2, BT * dh * 2, dh * 2, dh // 8
-    IPW = TILE // 1024 // 4
-    kswz = lambda r: ((r // 2) if KRB == 64 else (r // (256 // KRB))) % KCH
-    vswz = lambda d: ((d >> 1) ^ (d >> 4)) & 7
+    and each operand read finds the chunk the DMA put there."""
+    TILE, KB, KRB, NS, IPW = _ints(plan().ap_ring, 5, dh)
+    assert (TILE, KB, KRB, NS) == (256 * dh, 128 * dh, 2 * dh, ns) and 4 * IPW * 1024 == TILE
     placed = {}                                   # LDS byte offset in the stage -> source byte offset
     for wave, i, lane in itertools.product(range(4), range(IPW), range(64)):
         byte = (wave * IPW + i) * 1024 + lane * 16
-        if byte < KBYTES:
-            r, sl = byte // KRB, (byte % KRB) >> 4
-            src = r * KRB + ((sl ^ kswz(r)) << 4)
-        else:
-            vb = byte - KBYTES
-            d, sl = vb >> 7, (vb & 127) >> 4
-            src = KBYTES + d * 128 + ((sl ^ vswz(d)) << 4)
-        assert 0 <= src and src + 16 <= TILE
         assert byte not in placed
-        placed[byte] = src
+        placed[byte] = plan().ap_source(dh, byte)
     assert sorted(placed) == list(range(0, TILE, 16)) and sorted(placed.values()) == list(range(0, TILE, 16))
-    assert ns * TILE <= 64 * 1024 and 3 * IPW < 64
-    for lane in range(64):                        # key operand: row r, chunk c
-        for kt, kk in itertools.product(range(4), range(dh // 32)):
-            r, c = kt * 16 + (lane & 15), kk * 4 + (lane >> 4)
-            assert placed[r * KRB + ((c ^ kswz(r)) << 4)] == r * KRB + c * 16
-        g = lane >> 4                             # value operand: row d, keys 4g + 16q .. +3
-        for dt, q in itertools.product(range(dh // 16), range(4)):
-            d = dt * 16 + (lane & 15)
-            lds = KBYTES + d * 128 + ((((g >> 1) + 2 * q) ^ vswz(d)) << 4)
-            key0 = 4 * g + 16 * q
-            assert placed[lds] + (g & 1) * 8 == KBYTES + d * 128 + key0 * 2
+    assert NS * TILE <= 64 * 1024 and 3 * IPW < 64
+    _tile_reads_find(dh, placed)
     # (the swizzles' bank behaviour is a measured property of the hardware: a
     # one-wave probe of these reads shows no conflicts; the model of 64
     # 4-byte banks that first chose them does not describe gfx950's LDS)
+
+
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("threads", [256, 512])
+def test_in_block_tile_writes(dh, threads):
+    """A block's own keys and values in LDS (the encoder, the final split): key
+    chunks and 32-bit value pairs fill the tile once each, and the operand reads
+    find there what they would find in a page."""
+    TILE, KB, KRB, _, _ = _ints(plan().ap_ring, 5, dh)
+    CPR = dh // 8
+    NK, NJ = 64 * CPR, 64 * CPR + 32 * CPR
+    half = {}                                     # 2-byte LDS place -> byte of the tile in memory
+    for tid in range(threads):
+        for j in range(tid, NJ, threads):
+            if j < NK:
+                row, c8 = j // CPR, j % CPR
+                at = plan().ap_key_at(dh, plan().ap_tile_row(row), c8)
+                put = [(at + 2 * e, row * KRB + c8 * 16 + 2 * e) for e in range(8)]
+                assert at % 16 == 0 and at + 16 <= KB
+            else:
+                key, c8 = 2 * ((j - NK) // CPR), (j - NK) % CPR
+                put = []
+                for d in range(c8 * 8, c8 * 8 + 8):
+                    at = plan().ap_value_at(dh, d, key)
+                    assert at % 4 == 0 and KB <= at and at + 4 <= TILE
+                    put += [(at + 2 * e, KB + d * 128 + (key + e) * 2) for e in range(2)]
+            for at, what in put:
+                assert at not in half
+                half[at] = what
+    assert len(half) == TILE // 2
+    slots = {at: half[at] for at in range(0, TILE, 16)}
+    assert all(half[at + 2 * e] == slots[at] + 2 * e for at in slots for e in range(8))
+    _tile_reads_find(dh, slots)
+
+
+@pytest.mark.parametrize("all_", [512, 518, 600, 1200, 4095, 4096])
+def test_encoder_tile_ranges(all_):
+    """xcd_range: a permutation of the tiles in which each XCD (workgroup index
+    mod 8) has one contiguous range."""
+    got = [plan().ap_xcd_range(n, all_) for n in range(all_)]
+    assert sorted(got) == list(range(all_))
+    for x in range(8):
+        mine = got[x::8]
+        assert mine == list(range(mine[0], mine[0] + len(mine)))
 
 
 @pytest.mark.parametrize("b,dh,es", SHAPES)
@@ -942,59 +930,34 @@ def test_export_indexing_and_transpose(b, dh, es):
             assert [tile[(cc * E + j) * b + off] for j in range(E)] == [(cc * E + j, r) for j in range(E)]
 
 
-@pytest.mark.parametrize("dh,qw", [(32, 2), (32, 4), (64, 2), (64, 4)])
+@pytest.mark.parametrize("dh,qw", [(32, 1), (32, 2), (64, 1), (64, 2)])
 def test_prefill_par_lds_and_thread_ranges(dh, qw):
-    """The few-pair prefill (4 wave groups of qw waves): each group's DMA ring,
-    the in-block tile, the null row and the split-state slots stay inside the
-    workgroup's LDS; the in-block keys and transposed values are written once
-    each, where the ring's key and value operand reads look for them; the
-    launch indices cover every (pair, part) once, the parts of a pair on one
-    XCD; every query row is owned by one wave."""
-    BT, G = 64, 4
-    NSP = 4 if dh == 32 else 2
-    TILE, KBYTES, KRB, KCH = 2 * BT * dh * 2, BT * dh * 2, dh * 2, dh // 8
-    IPW = TILE // 1024 // qw
-    THREADS, ROWS = 64 * G * qw, 16 * qw
-    RING = G * NSP * TILE
-    OFF_IN = RING
-    OFF_NULL = OFF_IN + TILE
-    BYTES = OFF_NULL + 4 * dh
-    STATE = (dh // 16) * 1024 + 64 * 8
-    assert BYTES <= 160 * 1024 and (G + 1) * qw * STATE <= RING and 3 * IPW < 64
-    kswz = lambda r: ((r // 2) if KRB == 64 else (r // (256 // KRB))) % KCH
-    vswz = lambda d: ((d >> 1) ^ (d >> 4)) & 7
-    seen = set()
+    """The few-pair prefill (4 wave groups of qw waves, as launched up to 64
+    pairs and beyond): each group's DMA ring, the in-block tile, the null row and
+    the split-state slots stay inside the workgroup's LDS; each stage holds a
+    page whose operand reads find the chunk the DMA put there; the launch
+    indices cover every (pair, part) once, the parts of a pair on one XCD; every
+    query row is owned by one wave."""
+    BT = 64
+    TILE, KBYTES, KRB, _, _ = _ints(plan().ap_ring, 5, dh)
+    G, NSP, IPW, THREADS, ROWS, RING, OFF_IN, OFF_NULL, BYTES, STATE = _ints(plan().ap_par, 10, dh, qw)
+    assert G == 4 and THREADS == 64 * G * qw and ROWS == 16 * qw and IPW * qw * 1024 == TILE and 3 * IPW < 64
+    assert RING == G * NSP * TILE and OFF_IN >= RING and OFF_NULL >= OFF_IN + TILE and OFF_NULL + 4 * dh <= BYTES
+    assert BYTES <= 160 * 1024 and (G + 1) * qw * STATE <= RING and STATE >= (dh // 16) * 1024 + 64 * 8
+    placed = {}
     for g, w, stage, i, lane in itertools.product(range(G), range(qw), range(NSP), range(IPW), range(64)):
-        lds = g * NSP * TILE + w * IPW * 1024 + stage * TILE + i * 1024 + lane * 16
-        assert 0 <= lds and lds + 16 <= RING and lds not in seen
-        seen.add(lds)
-    assert len(seen) * 16 == RING
+        byte = (w * IPW + i) * 1024 + lane * 16       # of the stage
+        lds = (g * NSP + stage) * TILE + byte
+        assert 0 <= lds and lds + 16 <= RING and lds not in placed
+        placed[lds] = plan().ap_source(dh, byte)
+    assert len(placed) * 16 == RING
+    for g, stage in itertools.product(range(G), range(NSP)):
+        base = (g * NSP + stage) * TILE
+        page = {at - base: v for at, v in placed.items() if base <= at < base + TILE}
+        assert sorted(page.values()) == list(range(0, TILE, 16))
+        if g in (0, G - 1) and stage == NSP - 1:
+            _tile_reads_find(dh, page)
     CPR = dh // 8
-    NK, NJ = BT * CPR, BT * CPR + (BT // 2) * CPR
-    keys, vals = {}, {}
-    for tid in range(THREADS):
-        for j in range(tid, NJ, THREADS):
-            if j < NK:
-                row, c8 = j // CPR, j % CPR
-                off = row * KRB + ((c8 ^ kswz(row)) << 4)
-                assert 0 <= off and off + 16 <= KBYTES and off not in keys
-                keys[off] = (row, c8)
-            else:
-                pr, c8 = (j - NK) // CPR, (j - NK) % CPR
-                key = 2 * pr
-                for q in range(4):
-                    for d in (c8 * 8 + 2 * q, c8 * 8 + 2 * q + 1):
-                        off = KBYTES + d * 128 + (((key >> 3) ^ vswz(d)) << 4) + (key & 7) * 2
-                        assert KBYTES <= off and off + 4 <= TILE and off not in vals
-                        vals[off] = (d, key)
-    assert len(keys) * 16 == KBYTES and len(vals) * 4 == TILE - KBYTES
-    for lane, kt, kk in itertools.product(range(64), range(4), range(dh // 32)):   # scores_ring's reads
-        r, c = kt * 16 + (lane & 15), kk * 4 + (lane >> 4)
-        assert keys[r * KRB + ((c ^ kswz(r)) << 4)] == (r, c)
-    for lane, dt, q in itertools.product(range(64), range(dh // 16), range(4)):      # pv_ring's reads
-        gg, d = lane >> 4, dt * 16 + (lane & 15)
-        off = KBYTES + d * 128 + ((((gg >> 1) + 2 * q) ^ vswz(d)) << 4) + (gg & 1) * 8
-        assert vals[off] == (d, 4 * gg + 16 * q) and vals[off + 4] == (d, 4 * gg + 16 * q + 2)
     assert 2 * CPR <= THREADS and OFF_NULL + 2 * CPR * 16 <= BYTES                    # null row
     # split states: slots 0..3 the memory splits, slot 4 the final split; the
     # folding wave (g, w) reads dimension tile g < dh/16 of each
@@ -1005,10 +968,10 @@ def test_prefill_par_lds_and_thread_ranges(dh, qw):
         assert base + (dh // 16) * 1024 + 63 * 8 + 8 <= (j * qw + w + 1) * STATE
     npart = 4 // qw
     for n_pairs in (1, 7, 8, 9, 96, 128, 511):
-        grid = ((n_pairs + 7) // 8) * 8 * npart
+        grid = plan().ap_par_grid(n_pairs, qw)
         got = {}
         for n in range(grid):
-            pair, part = (n // (8 * npart)) * 8 + n % 8, (n // 8) % npart
+            pair, part = plan().ap_par_pair(n, qw), plan().ap_par_part(n, qw)
             if pair >= n_pairs:
                 continue
             assert (pair, part) not in got
@@ -1017,6 +980,7 @@ def test_prefill_par_lds_and_thread_ranges(dh, qw):
         assert all(got[(p, 0)] == got[(p, k)] for p in range(n_pairs) for k in range(npart))
     rows = sorted(part * ROWS + w * 16 + r for part in range(npart) for w in range(qw) for r in range(16))
     assert rows == list(range(BT))
+    assert [plan().ap_par_row_waves(n) for n in (1, 64, 65, 128)] == [1, 1, 2, 2]
 
 
 def _meta_items(live, edits, mb, chunk=1024, max_edits=128, max_items=128):
@@ -1114,8 +1078,8 @@ def test_encoder_output_staging(dh):
     lanes one pass serves, over 128 bytes of banks) touches each bank once.
     Without the swap the same check fails: two rows of a group share a slot
     modulo 128 bytes."""
-    BT, KRB, KCH = 64, dh * 2, dh // 8
-    kswz = lambda r: ((r // 2) if KRB == 64 else (r // (256 // KRB))) % KCH
+    BT, KRB = 64, dh * 2
+    key_at = lambda r, c: plan().ap_key_at(dh, r, c)
     SWB = 9 if dh == 32 else 7
 
     def layout(swap):
@@ -1125,7 +1089,7 @@ def test_encoder_output_staging(dh):
                 banks = []
                 for lane in range(16 * g, 16 * g + 16):
                     qrow, d0 = wave * 16 + (lane & 15), dt * 16 + (lane >> 4) * 4
-                    slot = qrow * KRB + (((d0 >> 3) ^ kswz(qrow)) << 4)
+                    slot = key_at(qrow, d0 >> 3)
                     off = slot + (((d0 >> 2) & 1) ^ (((slot >> SWB) & 1) if swap else 0)) * 8
                     assert 0 <= off and off + 8 <= BT * KRB
                     for i in range(4):
@@ -1139,13 +1103,13 @@ def test_encoder_output_staging(dh):
     where, clean = layout(True)
     assert clean and len(where) == BT * dh
     for row, c8 in itertools.product(range(BT), range(dh // 8)):       # 16-byte reads, halves swapped back
-        slot = row * KRB + ((c8 ^ kswz(row)) << 4)
+        slot = key_at(row, c8)
         elems = [where[slot + 2 * e] for e in range(8)]
         if (slot >> SWB) & 1:
             elems = elems[4:] + elems[:4]
         assert elems == [(row, c8 * 8 + e) for e in range(8)]
     for d, r in itertools.product(range(dh), range(BT)):               # the page insert's transposed gather
-        slot = r * KRB + (((d >> 3) ^ kswz(r)) << 4)
+        slot = key_at(r, d >> 3)
         assert where[slot + (((d & 7) * 2) ^ (((slot >> SWB) & 1) * 8))] == (r, d)
 
 
