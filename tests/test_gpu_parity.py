@@ -706,3 +706,20 @@ def test_put_export_every_shape_bitwise(dtype, b, dh, H, nb):
     smem.smem_store_put_blocks(st, [0] * nb, list(range(nb)), K, V)
     _, k, v = smem.smem_store_export(st, 0)
     assert torch.equal(k, K) and torch.equal(v, V)
+
+
+# More live blocks than one export launch takes (65535, the grid's second axis):
+# the second launch starts at the right entry and writes the right rows.
+def test_export_past_one_launch():
+    say("export past 65535 entries")
+    b, H, dh, n = 16, 1, 32, 65535 + 129
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    K, V = (torch.randn(n * b, H, dh, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    st = smem.Store(1, n, n, b, H, dh)
+    smem.smem_store_put_blocks(st, [0] * n, list(range(n)), K, V)
+    smem.smem_delete_block(st, 0, 17)            # so that entry i is not block i
+    idx, k, v = smem.smem_store_export(st, 0)
+    assert idx == [j for j in range(n) if j != 17]
+    keep = torch.arange(n * b, device="cuda").reshape(n, b)[torch.tensor(idx, device="cuda")].reshape(-1)
+    assert torch.equal(k, K[keep]) and torch.equal(v, V[keep])
