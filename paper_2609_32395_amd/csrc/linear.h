@@ -62,8 +62,12 @@ __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.f + er
 // is cut as a linear map cuts K: chunks of 256, each of 32 pieces of 8 values
 // (16 bytes).  A piece adds its values in ascending order; a chunk adds its
 // pieces as a binary tree (ln_tree32; missing pieces of a short last chunk as
-// zeros); the chunk totals add in ascending order from zero.  mean = total / d; the second moment sums (x - mean)^2 the
-// same way; rstd = 1 / sqrt(m2 / d + eps), the hardware's (1 ulp).
+// zeros); the chunk totals add in ascending order from zero.  mean = total / d;
+// the second moment sums (x - mean)^2 the same way; rstd = 1 / sqrt(m2 / d +
+// eps), each operation correctly rounded (the hardware's reciprocal square root
+// is not, and saves nothing: a 64-row read of a 19-layer model takes 787 us with
+// the division and 800 with the instruction, 8192 rows of LayerNorm, q|k|v and
+// attention 80.0 and 79.8).
 __device__ __forceinline__ void ln_unpack(const u32x4& c, float (&f)[8]) { Chunk<uint16_t>::unpack(c, f); }
 __device__ __forceinline__ float ln_piece(const float (&f)[8]) {
   float s = f[0];
@@ -138,7 +142,7 @@ __device__ __forceinline__ float ln_tree_operand(const float (&u)[8]) {
   const float z = v + __shfl_xor(v, 48);
   return z + __shfl_xor(z, 16);
 }
-__device__ __forceinline__ float ln_rstd(float m2, int d) { return __builtin_amdgcn_rsqf(m2 / d + 1e-5f); }
+__device__ __forceinline__ float ln_rstd(float m2, int d) { return 1.f / sqrtf(m2 / d + 1e-5f); }
 
 // Stand-alone LayerNorm (rows x[row * ldx .. + d) -> y[row * ldy ..)): one
 // wave per row, a half-wave per chunk, every load and store 512 contiguous

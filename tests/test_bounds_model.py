@@ -778,6 +778,14 @@ def test_layernorm_fused_indexing_and_order(M, N, K):
     assert got == want
 
 
+def test_layernorm_rstd_is_correctly_rounded():
+    """The LayerNorm's statistics use no approximate reciprocal or square-root
+    instruction: rstd is a correctly rounded square root and division."""
+    src = open(os.path.join(os.path.dirname(__file__), "..", "paper_2609_32395_amd", "csrc", "linear.h")).read()
+    body = src[src.index("void ln_unpack("):src.index("inline void launch_ln(")]
+    assert "1.f / sqrtf(" in body and "rsqf" not in body and "rcpf" not in body
+
+
 def test_gelu_erf_formula_in_source():
     """The erf of the GELU epilogue (Abramowitz & Stegun 7.1.26), evaluated
     with the constants read from linear.h, stays within the published bound
