@@ -1,7 +1,8 @@
 """Op-level parity of the model's kernels through the C ABI (smem_linear):
-the few-row linear map (k_linear_skinny), the same with the LayerNorm fused
-(k_linear_skinny_ln), the stand-alone LayerNorm (k_ln_rows, whose output the
-call returns in ln_tmp for more than 128 rows), the tiled GEMM (k_gemm) and
+the few-row linear map (k_linear_few, k_linear_wide), the same with the
+LayerNorm fused (k_linear_few_ln, k_linear_skinny_ln), the stand-alone LayerNorm
+(k_ln_rows, whose output the call returns in ln_tmp for more than 128 rows), the
+tiled GEMM (k_gemm) and
 the GELU / residual / fp32 epilogues, against the model oracle's fp64
 layer_norm, gelu and linear on the same bf16 input bytes.
 
