@@ -73,19 +73,19 @@ MFMA_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA, published (2.5 PFLOP/s,
 # a changed kernel reports traffic as null until measured again.  Figures
 # and commands: profiles/hbm_traffic_attention_kernels.md.
 CSRC = "paper_2609_32395_amd/csrc/"
+MFMA_SRCS = (CSRC + "attn_mfma.hip", CSRC + "attn_ring.h", CSRC + "attn_plan.h", CSRC + "common.h")
 TRAFFIC = {
     # 410M decode step: k_reader_valu + k_merge
-    "decode": ((CSRC + "reader_valu.hip", CSRC + "common.h"), {"77e591978f5a0ddc": 1.0890e+09}),
+    "decode": ((CSRC + "reader_valu.hip", CSRC + "common.h"), {"f0364f473a394e52": 1.0890e+09}),
     # 160M encoder: k_encoder_mfma (attention only)
-    "encoder": ((CSRC + "attn_mfma.hip", CSRC + "attn_ring.h", CSRC + "common.h"), {"2e5d7e7c4cc7fcae": 5.0445e+07}),
+    "encoder": (MFMA_SRCS, {"4804b076f1262fb9": 5.0436e+07}),
     # 160M final-block prefill: k_prefill_mfma_par
-    "prefill": ((CSRC + "attn_mfma.hip", CSRC + "attn_ring.h", CSRC + "common.h"), {"2e5d7e7c4cc7fcae": 2.6971e+07}),
+    "prefill": (MFMA_SRCS, {"4804b076f1262fb9": 2.6952e+07}),
     # 1.5B serve: k_prefill_mfma + k_merge
-    "serve": ((CSRC + "attn_mfma.hip", CSRC + "attn_ring.h", CSRC + "reader_valu.hip", CSRC + "common.h"),
-              {"d0b754a9272c091a": 3.0615e+08}),
+    "serve": (MFMA_SRCS + (CSRC + "reader_valu.hip",), {"4c3def702476354f": 3.0615e+08}),
     # 410M row-plane decode step: k_rows_absorb_q, k_reader_rows, k_rows_combine (with the
     # in-block keys), k_rows_project
-    "rows": ((CSRC + "rows.hip", CSRC + "reader_valu.hip", CSRC + "common.h"), {"39d68117510eaddf": 6.4302e+08}),
+    "rows": ((CSRC + "rows.hip", CSRC + "reader_valu.hip", CSRC + "common.h"), {"08a21f566b0a8cde": 6.4304e+08}),
 }
 
 
