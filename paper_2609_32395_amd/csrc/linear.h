@@ -760,10 +760,9 @@ static void launch_few_ln(const LinArgs& a, hipStream_t s) {
 // a CU, it takes tile after tile, and the next tile's first stages are fetched
 // while the last one's outputs are formed and stored.
 // Measured, us (before: 128 x 128 tiles of 4 waves, one operand set): 8192 x
-// 2048 x 8192 with the residual 285 -> 250 (1100 TFLOP/s; MFMA busy 56% of the
-// cycles, at the 1.92 GHz that this load leaves), 8192 x 8192 x 2048 with GELU
-// 321 -> 299, 8192 x 4096 x 1024 with GELU 90 -> 85, 8192 x 3072 x 1024 64 ->
-// 61, 4096 x 1024 x 1024 18.8 -> 14.6.
+// 2048 x 8192 with the residual 285 -> 250 (1100 TFLOP/s), 8192 x 8192 x 2048
+// with GELU 321 -> 299, 8192 x 4096 x 1024 with GELU 90 -> 85, 8192 x 3072 x
+// 1024 64 -> 61, 4096 x 1024 x 1024 18.8 -> 14.6.
 template <int N>
 __device__ __forceinline__ void wait_stages(int ahead) {
   if (ahead >= 3) wait_vm<3 * N < 63 ? 3 * N : 63>();

@@ -161,9 +161,7 @@ struct GemmCfg {
 };
 
 // The tiles of a many-row map.  A wide tile moves fewer bytes from L2 into
-// LDS per product (the DMA, not the LDS reads, is what the main loop waits
-// for: with it taken out the 128 x 256 loop runs at 1420 instead of 1080
-// TFLOP/s), a small one fills the 256 CUs on small outputs.
+// LDS per product, a small one fills the 256 CUs on small outputs.
 using GemmWide = GemmCfg<128, 256, 64, 3, 2, 4>;   // one workgroup of 8 waves per CU (144 KB of LDS)
 using GemmTall = GemmCfg<128, 128, 64, 4, 2, 4>;   // one of 8 waves per CU (128 KB)
 using GemmPair = GemmCfg<128, 128, 64, 2, 2, 2>;   // two of 4 waves per CU (64 KB each)
